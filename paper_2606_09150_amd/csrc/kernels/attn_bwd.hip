@@ -15,12 +15,11 @@
 //    -delta, which seed the S and dP accumulators;
 //  * dkdv: one workgroup of eight waves per window key tile (one per CU).
 //    Waves w and w + 4 share 32 keys.  The workgroup gathers the query tiles
-//    whose mask bit keeps its tile and, per 32-query block, wave w computes
-//    S = Q K^T and P, hands P to wave w + 4 through LDS and accumulates
+//    whose mask bit keeps its tile and walks them in half tiles: wave w
+//    computes S = Q K^T and P, hands P to wave w + 4 through LDS and accumulates
 //    dV^T += dO^T P, while wave w + 4 computes dP = dO V^T, dS = P (dP - delta)
-//    from the shared P and accumulates dK^T += Q^T dS; the two run one block
-//    apart, and the Q and dO rows of the next query tile are copied while the
-//    current one is used;
+//    from the shared P and accumulates dK^T += Q^T dS one half tile later; Q and
+//    dO rows are copied two half tiles ahead;
 //  * dq: one workgroup of four waves per query tile (two per CU), 32 queries
 //    per wave; it walks the row's list and per 32-key block computes
 //    S^T = K Q^T, dP^T = V dO^T, dS^T, then dQ^T += K^T dS^T.
@@ -206,30 +205,42 @@ __device__ inline bf16x8 row_op(const uint8_t* tile, const RowTable& U, int R, i
 
 // ---------------------------------------------------------------- dkdv ----
 
-// One workgroup per window key tile kj = ((pos*B + b)*H + h)*NT + t, T/16
-// waves (eight for 128-token tiles): wave w < T/32 (group 0) and wave
-// w + T/32 (group 1) share keys 32w + swap23(ln) (lane ln), so that the V operand read transposed from the
-// pool's V^T tile (whose columns hold the keys in swap23 order) lands in
-// natural lane order.  Per 32-query block, group 0 computes S = Q K^T and P,
-// hands P (bf16, already in the B-operand layout) to its partner through LDS
-// and accumulates dV^T += dO^T P; group 1 computes dP = dO V^T, then
-// dS = P (dP - delta) and dK^T += Q^T dS.  The S and dP accumulators start
-// from the workspace's -LSE/scale and -delta, so P = exp2(c2 S') and
-// dS = P dP' need no subtraction.  Both groups issue the same number of MFMAs
-// and one SIMD runs one wave of each.  The kept query tiles are gathered first
-// (mask bits); their Q and dO rows are double-buffered in LDS.
+// One workgroup per window key tile, T/16 waves (eight for 128-token tiles):
+// wave w < T/32 (group 0) and wave w + T/32 (group 1) share keys
+// 32w + swap23(ln) (lane ln), so that the V operand read transposed from the
+// pool's V^T tile (whose columns hold the keys in swap23 order) lands in natural
+// lane order.  The kept query tiles are gathered first (mask bits) as a list of
+// units of T/2 queries (half tiles; a half without a valid query gives none).
+// Per unit, group 0 computes S = Q K^T and P, hands P (bf16, already in the
+// B-operand layout) to its partner through LDS and accumulates dV^T += dO^T P;
+// group 1 computes dP = dO V^T and, one unit later, dS = P (dP - delta) and
+// dK^T += Q^T dS.  The S and dP accumulators start from the workspace's
+// -LSE/scale and -delta, so P = exp2(c2 S') and dS = P dP' need no subtraction.
+//
+// What bounds it: four products per pair on the matrix cores, under the power
+// limit (the clock falls as they get busier).  With five steps per query tile,
+// the first and last half empty, and each operand read right before its
+// product, they were busy 51 % of the cycles at 1.98 GHz and the 1K window (12
+// heads, 24,480-token chunks, 55 % kept) took 19.2 ms; with the phases below
+// 63 % at 1.76 GHz, 17.4 ms.  (The phases alone, in the compiler's order of
+// reads: 47 %, 20.0 ms; with the reads ahead 59 %, 18.1 ms; the copies between
+// the products instead of at the start of the phase: 63 %.)
+//
+// Phases.  Phase s is unit s for group 0 and for group 1's dP, unit s-1 for
+// group 1's dS and dK, with one workgroup barrier after it; both groups issue
+// the same number of MFMAs in it, and one SIMD runs one wave of each.  Units
+// follow one another without a drain between query tiles.  Q rows live in a ring
+// of four units (s-1, s, s+1 and the one being copied), dO rows in a ring of
+// three, so that a unit is requested two phases before it is used.
+constexpr int kQRing = 4, kORing = 3, kLRing = 4;
+constexpr int kAhead = 6;   // operands in flight ahead of their product
+
+// The rows of a unit: W = T/16 waves fill UQ = T/2 rows of 256 bytes; copy i of
+// wave w fills LDS chunks [64*(W i + w), +64), rows 4(W i + w) + lane/16, whose
+// low four bits do not depend on i.
 __device__ inline uint32_t copy_offset8(int wave, int lane) {
   const int r = 4 * wave + (lane >> 4);
   return uint32_t(r * 256 + swz_perm((lane & 15) ^ swz_f(r & 15)) * 16);
-}
-// A T-row tile of 256-byte rows with W = T/16 waves: copy i of wave w fills
-// LDS chunks [64*(W i + w), +64), rows 4(W i + w) + lane/16; the row's low
-// four bits do not depend on i.
-template <int W>
-__device__ inline void copy_tile_w(const uint8_t* src, uint32_t lds_tile, uint32_t voff, int wave) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    dma16(src + i * (W * 1024), voff, lds_tile + uint32_t(wave) * 1024u + uint32_t(i) * uint32_t(W * 1024));
 }
 // The V^T of a 64-token page ([128 dims][64 keys], 128-byte rows) into the
 // swizzled [128][128] tile layout, of which it fills the first 64 columns,
@@ -253,29 +264,66 @@ __device__ inline void copy_tile8_page(const uint8_t* src, uint32_t lds_tile, ui
   for (int i = 0; i < 4; ++i) dma16(src + i * 4096, voff, lds_tile + uint32_t(wave) * 1024u + uint32_t(i) * 8192u);
 }
 
+// s_waitcnt vmcnt(N) lgkmcnt(0), then the workgroup barrier; the signal fences
+// keep the compiler from moving LDS accesses across it.
+template <int N>
+__device__ __forceinline__ void meet() {
+  constexpr int imm = (N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14);
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(imm);
+  __builtin_amdgcn_s_barrier();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+// dma16 of the lanes in `mask` only (the whole wave is active around it).
+__device__ inline void dma16_low(const void* base, uint32_t off, uint32_t lds, uint64_t mask) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
+               : : "v"(off), "s"(base), "s"(lds), "s"(mask) : "memory");
+}
+
+// LDS reads by byte address (an address of zero is an ordinary one).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+__device__ inline u32x4 lds_read16(uint32_t at) { return *(const lds_u32x4*)(uintptr_t)at; }
+__device__ inline f32x4 lds_read4f(uint32_t at) { return *(const lds_f32x4*)(uintptr_t)at; }
+// tr_op with the tile's LDS address already in the table, R a multiple of 16
+__device__ inline bf16x8 tr_op_at(const TrTable& T, int R, int cb) {
+  const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(uintptr_t)(T.t[0][cb] + uint32_t(R * 256)));
+  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(uintptr_t)(T.t[1][cb] + uint32_t(R * 256)));
+  const v4i16 v[2] = {lo, hi};
+  return __builtin_bit_cast(bf16x8, v);
+}
+
 template <int T>
-__global__ __launch_bounds__(4 * T, 1) void bwd_dkdv_kernel(BwdArgs a) {
+__global__ __launch_bounds__(4 * T, 2) void bwd_dkdv_kernel(BwdArgs a) {
   constexpr int kKW = T / 32;                        // key blocks = waves of a group
-  constexpr int kQB = T / 32;                        // 32-query blocks of a query tile
-  // Q and dO rows, two query tiles (128 KB); the second dO buffer first holds
-  // the page's V^T (128 rows)
-  __shared__ uint4 sQ[2][kT * 16], sO[2][kT * 16];
-  __shared__ uint4 sP[4 * 2 * 2 * 64];               // P operands: [wave pair][block of the half][kk][lane]
-  __shared__ float sLD[2][2 * kT];                   // -LSE/scale, then -delta, per buffer
-  __shared__ uint16_t sList[kBwdMaxQTiles];
+  constexpr int W = 2 * kKW;                         // waves
+  constexpr int UQ = T / 2;                          // queries of a unit
+  constexpr int NB = UQ / 32;                        // 32-query blocks of a unit
+  constexpr uint32_t UB = UQ * 256;                  // bytes of a unit's Q (or dO) rows
+  constexpr int kCopies = UB / 1024 / W;             // copies of a wave per unit and operand
+  __shared__ uint4 sQ[kQRing][UQ * 16];
+  __shared__ uint4 sO[kORing][UQ * 16];
+  __shared__ uint4 sP[2][kKW][NB * 2][64];           // P operands of a unit: [parity][wave pair][block, kk][lane]
+  __shared__ float sLD[kLRing][2 * kT];              // the tile's -LSE/scale, then -delta, per unit
+  __shared__ uint16_t sList[2 * kBwdMaxQTiles];      // (query tile << 1) | half
   __shared__ int sN;
 
+  // the current chunk's tiles first: they (and the pinned chunk's, next at
+  // position 0) are kept by every query tile and run longest
   const int kj = blockIdx.x;
   const int t = kj % a.NT;
   const int posbh = kj / a.NT;
   const int bh = posbh % (a.B * a.H);
-  const int pos = posbh / (a.B * a.H);
+  const int order = posbh / (a.B * a.H);
+  const int pos = order == 0 ? a.n_live - 1 : order - 1;
   const int h = bh % a.H, b = bh / a.H;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = wave / kKW, kw = wave % kKW;
   const int lane = tid & 63, hl = lane >> 5, ln = lane & 31;
-  const uint32_t voff = copy_offset8(wave, lane);
   const int kvalid = tile_valid(a.tv, t, a.NT, a.tail, T);
   const int key = kw * 32 + swap23(ln);         // this lane's key (result column)
   const bool key_ok = key < kvalid;
@@ -283,7 +331,8 @@ __global__ __launch_bounds__(4 * T, 1) void bwd_dkdv_kernel(BwdArgs a) {
   const uint8_t* qbase = a.work + size_t(bh) * a.NT * kBwdQTile;
 
   // B operands of the wave's keys: group 0 K rows from the page, group 1 V
-  // read transposed from the page's V^T staged in the second dO buffer
+  // read transposed from the page's V^T, staged in the P slots (128-token
+  // tiles) or in the Q ring (64-token tiles, before any unit is copied)
   const uint8_t* page = a.pool + ((size_t(a.slot_of[pos]) * a.B * a.H + bh) * a.NT + t) * page_bytes(T, kD);
   bf16x8 bop[8];
   if (grp == 0) {
@@ -293,12 +342,14 @@ __global__ __launch_bounds__(4 * T, 1) void bwd_dkdv_kernel(BwdArgs a) {
       bop[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(page + off));
     }
   }
+  static_assert(T == 128 ? sizeof(sP) == kTile : sizeof(sQ) == kTile, "V^T stage");
+  uint4* const stage = T == 128 ? &sP[0][0][0][0] : &sQ[0][0];
   if constexpr (T == 128)
-    copy_tile8_page(page + kTile, lds_addr(&sO[1][0]), copy_offset8_page(wave, lane), wave);
+    copy_tile8_page(page + kTile, lds_addr(stage), copy_offset8_page(wave, lane), wave);
   else
-    copy_vt64_w4(page + T * kD * 2, lds_addr(&sO[1][0]), copy_offset_vt64(wave, lane), wave);
+    copy_vt64_w4(page + T * kD * 2, lds_addr(stage), copy_offset_vt64(wave, lane), wave);
 
-  // kept query tiles, ascending
+  // units of the kept query tiles, ascending
   if (wave == 0) {
     int cnt = 0;
     for (int base = 0; base < a.NT; base += 512) {
@@ -310,145 +361,267 @@ __global__ __launch_bounds__(4 * T, 1) void bwd_dkdv_kernel(BwdArgs a) {
       }
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const bool keep = (w[k] >> (j & 31)) & 1u;
-        const uint64_t bal = __ballot(keep);
-        if (keep) sList[cnt + __popcll(bal & ((uint64_t(1) << lane) - 1))] = uint16_t(base + 64 * k + lane);
-        cnt += __popcll(bal);
+        const int i = base + 64 * k + lane;
+        int n = 0;
+        if ((w[k] >> (j & 31)) & 1u) {
+          const int v = tile_valid(a.tv, i, a.NT, a.tail, T);
+          n = v > UQ ? 2 : (v > 0 ? 1 : 0);
+        }
+        const uint64_t b1 = __ballot(n >= 1), b2 = __ballot(n == 2);
+        const uint64_t below = (uint64_t(1) << lane) - 1;
+        const int at = cnt + __popcll(b1 & below) + __popcll(b2 & below);
+        if (n >= 1) sList[at] = uint16_t(i << 1);
+        if (n == 2) sList[at + 1] = uint16_t((i << 1) | 1);
+        cnt += __popcll(b1) + __popcll(b2);
       }
     }
     if (lane == 0) sN = cnt;
   }
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-  __syncthreads();
+  meet<0>();
+  const int U = __builtin_amdgcn_readfirstlane(sN);
+
+  // Copies of unit n (list entry e): Q and dO rows, and by wave 0 the tile's
+  // per-query values.
+  const uint32_t voff = copy_offset8(wave, lane);
+  const uint32_t lq0 = lds_addr(&sQ[0][0]), lo0 = lds_addr(&sO[0][0]), ll0 = lds_addr(&sLD[0][0]);
+  // Past the end the last unit is copied again, into a slot that nothing reads
+  // any more: every phase issues the same copies, without a branch.
+  struct Source {
+    const uint8_t* rec;
+    uint32_t half, qslot, oslot;
+  };
+  auto entry = [&](int n) { return uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(sList[min(n, U - 1)]))); };
+  auto source = [&](uint32_t e, uint32_t qslot, uint32_t oslot) {
+    return Source{qbase + size_t(e >> 1) * kBwdQTile, (e & 1) * UB, qslot, oslot};
+  };
+  constexpr int kIssue = 2 * kCopies + 1;       // copies of a wave per unit
+  auto issue = [&](const Source& c, int k) {    // copy k of them
+    if (k == 2 * kCopies) {
+      constexpr uint32_t part = 2 * kT * 4 / W; // this wave's share of the per-query values
+      dma16_low(c.rec + 2 * kTile + uint32_t(wave) * part, uint32_t(lane) * 16u,
+                ll0 + c.qslot * uint32_t(sizeof(sLD[0])) + uint32_t(wave) * part, (uint64_t(1) << (part / 16)) - 1);
+      return;
+    }
+    const uint32_t at = uint32_t(k >> 1) * W * 1024u;
+    dma16(c.rec + (k & 1) * kTile + c.half + at, voff,
+          ((k & 1) ? lo0 + c.oslot * UB : lq0 + c.qslot * UB) + uint32_t(wave) * 1024u + at);
+  };
+  auto issue_all = [&](const Source& c) {
+#pragma unroll
+    for (int k = 0; k < kIssue; ++k) issue(c, k);
+  };
+  uint32_t e0 = 0, e1 = 0, e2 = 0;
+  if (U > 0) {
+    e0 = entry(0);
+    e1 = entry(1);
+    e2 = entry(2);
+  }
+  if (T == 128 && U > 0) {                      // the stage is outside the rings
+    issue_all(source(e0, 0, 0));
+    issue_all(source(e1, 1, 1));
+  }
   if (grp == 1) {
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks)
-      bop[ks] = tr_operand((const lds_u8*)&sO[1][0], kw * 32, lane, [&](int kap) { return 16 * ks + kap; });
+      bop[ks] = tr_operand((const lds_u8*)stage, kw * 32, lane, [&](int kap) { return 16 * ks + kap; });
   }
-  const int N = __builtin_amdgcn_readfirstlane(sN);
-  __syncthreads();                              // V^T consumed: the second buffer is free
-
-  auto record = [&](int n) { return qbase + size_t(__builtin_amdgcn_readfirstlane(int(sList[n]))) * kBwdQTile; };
-  auto issue = [&](int n) {
-    const uint8_t* rec = record(n);
-    copy_tile_w<T / 16>(rec, lds_addr(&sQ[n & 1][0]), voff, wave);
-    copy_tile_w<T / 16>(rec + kTile, lds_addr(&sO[n & 1][0]), voff, wave);
-    if (wave == 0) dma16(rec + 2 * kTile, uint32_t(lane) * 16u, lds_addr(&sLD[n & 1][0]));
-  };
+  if (T == 64 && U > 0) {
+    meet<0>();                                  // V^T consumed
+    issue_all(source(e0, 0, 0));
+    issue_all(source(e1, 1, 1));
+  }
 
   f32x16 acc[4];                                // dV^T (group 0) or dK^T (group 1): [dim block][32 dims x 32 keys]
 #pragma unroll
   for (int mb = 0; mb < 4; ++mb) acc[mb] = f32x16{};
   const float c2 = a.scale_log2;
-  uint4* pslot = &sP[(kw * 2 * 2) * 64];        // this wave pair's P operands
-  const TrTable TT = tr_table<true>(lane);      // X^T reads: k-slot kappa = query 16kk + swap23(kappa)
-  const RowTable RT = row_table<false>(lane);   // X rows: query qb*32 + ln
+  const float pad = key_ok ? 0.f : -INFINITY;   // padding keys (lanes) weigh nothing; no branch in the phase
+  uint4* const pslot = &sP[0][kw][0][lane];     // this wave pair's P operands
+  constexpr uint32_t kPStep = sizeof(sP[0]) / 16;
+  // Operand addresses within the current ring slots, advanced once per phase:
+  // tr: transposing reads (X^T: k-slot kappa = query 16kk + swap23(kappa)) of
+  // dO (group 0) or Q (group 1); rt: row reads (X rows: query ln of a block) of
+  // Q (group 0) or dO (group 1); ld: the per-query seeds of the row reads.
+  TrTable tr = tr_table<true>(lane);
+  RowTable rt = row_table<false>(lane);
+  {
+    const uint32_t bt = grp == 0 ? lo0 : lq0, br = grp == 0 ? lq0 : lo0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb) tr.t[k][cb] += bt;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) rt.u[ks] += br;
+  }
+  const uint32_t ld0 = ll0 + uint32_t(16 * hl + (grp == 0 ? 0 : 4 * kT));
 
-  // acc^T += X^T op over the block's 32 queries (X = Q or dO rows, read transposed)
-  auto accumulate = [&](const lds_u8* x, int qb, const bf16x8 (&op)[2]) {
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-        acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_op(x, TT, qb * 32 + 16 * kk, mb), op[kk], acc[mb], 0, 0, 0);
+  // A unit's products of one wave: 8 NB row products (X K^T or X V^T, chain
+  // qb over ks), then 8 NB transposed ones (acc^T += X^T op, block qb, step kk,
+  // dims 32 mb ..).  Product i and its operand, read kAhead products earlier.
+  constexpr int kRows = 8 * NB, kAll = 16 * NB;
+  auto load = [&](int i) -> bf16x8 {
+    if (i < kRows) return __builtin_bit_cast(bf16x8, lds_read16(rt.u[i & 7] + uint32_t((i >> 3) * 32 * 256)));
+    const int k = i - kRows;
+    return tr_op_at(tr, 16 * (k >> 2), k & 3);
   };
-  // c0 + X K^T (group 0: S - LSE/scale from Q rows) or c0 + X V^T (group 1:
-  // dP - delta from dO rows) for 32 queries; c0 holds the per-query term in
-  // the result layout (register 4g + e = query qb*32 + 8g + 4hl + e), read
-  // from the workspace's per-query values.
-  auto product = [&](const uint8_t* x, const float* c, int qb) {
-    f32x16 v;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 c4 = *reinterpret_cast<const float4*>(&c[qb * 32 + 8 * g + 4 * hl]);
-      v[4 * g] = c4.x;
-      v[4 * g + 1] = c4.y;
-      v[4 * g + 2] = c4.z;
-      v[4 * g + 3] = c4.w;
-    }
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
-      v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_op(x, RT, qb * 32, ks), bop[ks], v, 0, 0, 0);
-    return v;
+  auto row_product = [&](int i, const bf16x8& x, f32x16 (&v)[NB]) {
+    v[i >> 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, bop[i & 7], v[i >> 3], 0, 0, 0);
   };
-  // group 0, block qb: S, P (as bf16 B operands, also written to the block's P slot)
-  auto scores = [&](const uint8_t* lq, const float* ld, int qb, bf16x8 (&op)[2]) {
-    const f32x16 sv = product(lq, ld, qb);      // S - LSE/scale (-inf on padding queries)
-    f32x16 p;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(sv[r] * c2);
-    if (kvalid < T) {                           // padding keys (lanes) weigh nothing
-#pragma unroll
-      for (int r = 0; r < 16; ++r) p[r] = key_ok ? p[r] : 0.f;
-    }
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      op[kk] = rows_to_operand(p, kk);
-      pslot[((qb & 1) * 2 + kk) * 64 + lane] = __builtin_bit_cast(uint4, op[kk]);
-    }
+  auto tr_product = [&](int i, const bf16x8& x, const bf16x8 (&op)[NB][2]) {
+    const int k = i - kRows, mb = k & 3;
+    acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, op[k >> 3][(k >> 2) & 1], acc[mb], 0, 0, 0);
   };
-  // group 1, block qb: dS = P (dP - delta) from the block's P slot, dK^T += Q^T dS
-  auto dk_block = [&](const lds_u8* lq, int qb, const f32x16& dpv) {
-    f32x16 ds;
+  // The row products start from the per-query terms, in the result layout:
+  // register 4g + e = query qb*32 + 8g + 4hl + e.
+  auto seed = [&](uint32_t ld, f32x16 (&v)[NB]) {
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      // k-slot e of operand kk is result register 8kk + e
-      const bf16x8 pk = __builtin_bit_cast(bf16x8, pslot[((qb & 1) * 2 + kk) * 64 + lane]);
+    for (int qb = 0; qb < NB; ++qb)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) ds[8 * kk + e] = float(pk[e]) * dpv[8 * kk + e];
-    }
-    const bf16x8 op[2] = {rows_to_operand(ds, 0), rows_to_operand(ds, 1)};
-    accumulate(lq, qb, op);
-  };
-
-  // Per tile, kQB + 1 steps (five for 128-token tiles) separated by
-  // meetings; P slot qb&1 carries block qb from group 0 (step qb) to group 1
-  // (step qb+1):
-  //   step 0:   group 0 S, P of block 0            | group 1 dP of block 0
-  //   step s:   group 0 S, P of block s, dV of s-1 | group 1 dS, dK of s-1, dP of s
-  //   step kQB: group 0 dV of the last block       | group 1 dS, dK of the last block
-  // so that in the middle steps both waves of a SIMD have 16 MFMAs.
-  // The buffer of tile n is n&1; the loop runs two tiles per trip so that the
-  // buffer, and with it every operand address, is a compile-time offset.
-  // Each group runs its own copy of the tile loop (same meetings in the same
-  // order), so that no branch on the group sits inside the loop and the
-  // accumulators keep their registers.
-  auto tile = [&](int n, auto buf, auto group) {
-    constexpr int B = decltype(buf)::value;
-    constexpr int G = decltype(group)::value;
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-    __syncthreads();                            // tile n in LDS; tile n-1 fully consumed
-    if (n + 1 < N) issue(n + 1);
-    const uint8_t* lq = reinterpret_cast<const uint8_t*>(&sQ[B][0]);
-    const uint8_t* lo = reinterpret_cast<const uint8_t*>(&sO[B][0]);
-    const float* ld = &sLD[B][0];
-    bf16x8 op[2][2];                            // group 0: P operands of the last two blocks
-    f32x16 dpv[2];                              // group 1: dP - delta of the last two blocks
-#pragma unroll
-    for (int st = 0; st <= kQB; ++st) {
-      if constexpr (G == 0) {
-        if (st < kQB) scores(lq, ld, st, op[st & 1]);
-        if (st > 0) accumulate((const lds_u8*)lo, st - 1, op[(st - 1) & 1]);   // dV^T += dO^T P
-      } else {
-        if (st > 0) dk_block((const lds_u8*)lq, st - 1, dpv[(st - 1) & 1]);
-        if (st < kQB) dpv[st & 1] = product(lo, ld + kT, st);
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 c4 = lds_read4f(ld + uint32_t(4 * (qb * 32 + 8 * g)));
+        v[qb][4 * g] = c4.x;
+        v[qb][4 * g + 1] = c4.y;
+        v[qb][4 * g + 2] = c4.z;
+        v[qb][4 * g + 3] = c4.w;
       }
-      if (st < kQB) __syncthreads();            // P of block st written; block st-1 consumed
+  };
+  // Two elements (registers 2e, 2e+1) of a block's operand.
+  auto put = [&](bf16x8 (&op)[2], int e, float x0, float x1) {
+    op[e >> 2][2 * (e & 3)] = (__bf16)x0;
+    op[e >> 2][2 * (e & 3) + 1] = (__bf16)x1;
+  };
+  auto advance = [&](uint32_t (&x)[8], bool wrap, int ring) {
+    const uint32_t d = wrap ? uint32_t(-(ring - 1) * int(UB)) : UB;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] += d;
+  };
+  auto advance_tr = [&](bool wrap, int ring) {
+    const uint32_t d = wrap ? uint32_t(-(ring - 1) * int(UB)) : UB;
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb) tr.t[k][cb] += d;
+  };
+
+  // Scheduling fences pin the order written here: a product, the read of a
+  // later one's operand, a piece of vector work.  Left to itself the compiler
+  // reads each operand right before its product and runs the vector work
+  // between them, so that a product waits for an LDS round trip.
+  auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
+  constexpr int kGap = kAll / kIssue;           // products between two of the next unit's copies
+  // Group 0, unit s: S, P, the P slot, dV.  The weights of a block are formed
+  // beside the next block's products.
+  auto unit0 = [&](uint32_t ld, uint32_t par, const Source& next) {
+    f32x16 sv[NB];
+    bf16x8 op[NB][2], x[kAll];
+    seed(ld, sv);                               // -LSE/scale (-inf on padding queries)
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) x[i] = load(i);
+    auto weights = [&](int qb, int e) {
+      put(op[qb], e, __builtin_amdgcn_exp2f(__builtin_fmaf(sv[qb][2 * e], c2, pad)),
+          __builtin_amdgcn_exp2f(__builtin_fmaf(sv[qb][2 * e + 1], c2, pad)));
+      if ((e & 3) == 3) pslot[par * kPStep + (qb * 2 + (e >> 2)) * 64] = __builtin_bit_cast(uint4, op[qb][e >> 2]);
+    };
+    fence();
+#pragma unroll
+    for (int i = 0; i < kAll; ++i) {
+      if (i < kRows) row_product(i, x[i], sv);
+      else tr_product(i, x[i], op);
+      if (i + kAhead < kAll) x[i + kAhead] = load(i + kAhead);
+      if (i >= 8 && i < kAll - 8) weights((i - 8) >> 3, i & 7);
+      if (NB == 1 && i == 7) {                  // one block: nothing to run beside
+#pragma unroll
+        for (int e = 0; e < 8; ++e) weights(0, e);
+      }
+      if (i % kGap == kGap - 1 && i / kGap < kIssue) issue(next, i / kGap);
+      fence();
     }
   };
-  auto run = [&](auto group) {
-    for (int n = 0; n < N; n += 2) {
-      tile(n, std::integral_constant<int, 0>{}, group);
-      if (n + 1 < N) tile(n + 1, std::integral_constant<int, 1>{}, group);
+  // Group 1: dP - delta of a unit (kDp) into nv, and dS (from the P slot and
+  // the dP of the unit before, ov) and dK of that unit (kDk).
+  auto unit1 = [&](auto dp, auto dk, uint32_t ld, uint32_t par, const f32x16 (&ov)[NB], f32x16 (&nv)[NB],
+                   const Source& next) {
+    constexpr bool kDp = decltype(dp)::value, kDk = decltype(dk)::value;
+    constexpr int i0 = kDp ? 0 : kRows, i1 = kDk ? kAll : kRows;
+    bf16x8 pk[NB][2], op[NB][2], x[kAll];
+    if (kDk) {
+#pragma unroll
+      for (int qb = 0; qb < NB; ++qb)
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+          pk[qb][kk] = __builtin_bit_cast(bf16x8, pslot[par * kPStep + (qb * 2 + kk) * 64]);
+    }
+    if (kDp) seed(ld, nv);                      // -delta
+#pragma unroll
+    for (int i = i0; i < i0 + kAhead; ++i) x[i] = load(i);
+    auto ds = [&](int qb, int e) {              // k-slot of operand kk: result register 8kk + slot
+      put(op[qb], e, float(pk[qb][e >> 2][2 * (e & 3)]) * ov[qb][2 * e],
+          float(pk[qb][e >> 2][2 * (e & 3) + 1]) * ov[qb][2 * e + 1]);
+    };
+    fence();
+    if (kDk && !kDp) {
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) ds(k >> 3, k & 7);
+    }
+#pragma unroll
+    for (int i = i0; i < i1; ++i) {
+      if (i < kRows) row_product(i, x[i], nv);
+      else tr_product(i, x[i], op);
+      if (i + kAhead < i1) x[i + kAhead] = load(i + kAhead);
+      if (kDk && i < kRows) ds(i >> 3, i & 7);
+      if (kDp && kDk && i % kGap == kGap - 1 && i / kGap < kIssue) issue(next, i / kGap);
+      fence();
     }
   };
 
-  if (N > 0) issue(0);
-  if (grp == 0) run(std::integral_constant<int, 0>{});
-  else run(std::integral_constant<int, 1>{});
+  // Each group runs its own copy of the phase loop (same meetings in the same
+  // order), so that no branch on the group sits inside it.
+  auto run = [&](auto group) {
+    constexpr int G = decltype(group)::value;
+    f32x16 dpv[NB];
+    uint32_t om = 0;                            // s % 3
+    auto phase = [&](int s, auto first) {
+      constexpr bool kFirst = decltype(first)::value;
+      // unit s has landed; the slots of unit s+2 are free
+      const Source next = source(e2, uint32_t(s + 2) & 3u, om == 0 ? 2u : om - 1u);
+      const uint32_t ld = ld0 + (uint32_t(s) & 3u) * uint32_t(sizeof(sLD[0])) + (e0 & 1u) * uint32_t(4 * UQ);
+      const uint32_t e3 = sList[min(s + 3, U - 1)];
+      if constexpr (G == 0) {
+        unit0(ld, uint32_t(s) & 1u, next);
+        advance(rt.u, (s & 3) == 3, kQRing);
+        advance_tr(om == 2, kORing);
+      } else {
+        f32x16 nv[NB];
+        if constexpr (kFirst) issue_all(next);
+        unit1(std::true_type{}, std::bool_constant<!kFirst>{}, ld, uint32_t(s - 1) & 1u, dpv, nv, next);
+#pragma unroll
+        for (int qb = 0; qb < NB; ++qb) dpv[qb] = nv[qb];
+        if constexpr (!kFirst) advance_tr((s & 3) == 0, kQRing);
+        advance(rt.u, om == 2, kORing);
+      }
+      om = om == 2 ? 0 : om + 1;
+      meet<kIssue>();                           // unit s+1 has landed; unit s+2 may be in flight
+      e0 = e1;
+      e1 = e2;
+      e2 = __builtin_amdgcn_readfirstlane(e3);
+    };
+    meet<kIssue>();                             // unit 0 has landed, unit 1 may be in flight
+    phase(0, std::true_type{});
+    for (int s = 1; s < U; ++s) phase(s, std::false_type{});
+    if constexpr (G == 1) {
+      f32x16 nv[NB];
+      unit1(std::false_type{}, std::true_type{}, 0, uint32_t(U - 1) & 1u, dpv, nv, Source{});
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // no copy outlives the workgroup
+  };
+
+  if (U > 0) {
+    if (grp == 0) run(std::integral_constant<int, 0>{});
+    else run(std::integral_constant<int, 1>{});
+  }
 
   // store: lane holds key `key`, dims mb*32 + 8*(r/4) + 4*hl + r%4; padding
-  // rows inside the chunk (block order) get the zeros they accumulated
+  // rows inside the chunk (block order) get zeros
   const size_t tok = size_t(t) * T + key;
   if (tok < size_t(a.L)) {
     float* dst = (grp ? a.dk : a.dv) + (((size_t(pos) * a.B + b) * a.L + tok) * a.H + h) * kD;
@@ -458,7 +631,9 @@ __global__ __launch_bounds__(4 * T, 1) void bwd_dkdv_kernel(BwdArgs a) {
 #pragma unroll
       for (int g = 0; g < 4; ++g)
         *reinterpret_cast<float4*>(dst + mb * 32 + 8 * g + 4 * hl) =
-            make_float4(acc[mb][4 * g] * f, acc[mb][4 * g + 1] * f, acc[mb][4 * g + 2] * f, acc[mb][4 * g + 3] * f);
+            key_ok ? make_float4(acc[mb][4 * g] * f, acc[mb][4 * g + 1] * f, acc[mb][4 * g + 2] * f,
+                                 acc[mb][4 * g + 3] * f)
+                   : make_float4(0.f, 0.f, 0.f, 0.f);
   }
 }
 

@@ -105,6 +105,30 @@ def test_small_backward_parity(B, L, H, mc, pin, n, p, T):
     _full_compare(case, case.rule(p))
 
 
+# Half-tile units of the key-side kernel: 1 to 7 units per list (its rings hold
+# three and four), last tiles that end at, just before and just after a half.
+# A key that only a one-query tile keeps has a single dS term, in which dP - delta
+# may cancel while delta keeps the rounding of the bf16 O: the bar is the one of
+# the peaked rows below, over the larger of the row and its summand scale.
+@pytest.mark.parametrize("p", [1.0, 0.4])
+@pytest.mark.parametrize("T,L", [(128, n) for n in (63, 64, 65, 128, 129, 192, 193, 385)] +
+                         [(64, n) for n in (31, 32, 33, 64, 65, 96, 97, 225)])
+def test_backward_half_tile_units(T, L, p):
+    P = require_gpu()
+    log(f"bwd units T={T} L={L} p={p}")
+    case = Case(P, 1, L, 2, T, 3, True, seed=2400 + L)
+    for _ in range(4):
+        case.append()
+    rule, scale = case.rule(p), 1 / math.sqrt(128)
+    q, o, lse, do, *grads = _run(case, rule, scale)
+    args = (case.ring, case._host(q), case._host(do), case.oracle_bits(rule), T, scale)
+    refs = oracle.sparse_causal_attention_bwd(*args)
+    scales = oracle.sparse_causal_attention_bwd_scales(*args)
+    worst = [float(row_errors_scaled(g.cpu().numpy(), r, s).max()) for g, r, s in zip(grads, refs, scales)]
+    log("  per-row " + " ".join(f"{x:.3e}" for x in worst))
+    assert max(worst) <= GRAD_TOL, worst
+
+
 def test_backward_tiny_workload():
     """The tiny window (64-token tiles, 2 heads, 384 keys, every tile kept) in full."""
     P = require_gpu()
