@@ -20,9 +20,10 @@
 //    dV^T += dO^T P, while wave w + 4 computes dP = dO V^T, dS = P (dP - delta)
 //    from the shared P and accumulates dK^T += Q^T dS one half tile later; Q and
 //    dO rows are copied two half tiles ahead;
-//  * dq: one workgroup of four waves per query tile (two per CU), 32 queries
-//    per wave; it walks the row's list and per 32-key block computes
-//    S^T = K Q^T, dP^T = V dO^T, dS^T, then dQ^T += K^T dS^T.
+//  * dq: one workgroup of four waves per query tile (two per CU; four waves with
+//    either tile size), 32 queries per wave; it walks the row's list in units of
+//    64 keys and per 32-key block computes S^T = K Q^T, dP^T = V dO^T, dS^T, then
+//    dQ^T += K^T dS^T, while the next unit is copied;
 // The transposed operands (dO^T, Q^T, K^T, and V rows from the pool's V^T)
 // come from row-major LDS tiles through the transposing LDS read
 // (ds_read_b64_tr_b16), so each tile is copied into LDS once, in the layout the
@@ -102,29 +103,13 @@ __global__ __launch_bounds__(kThreads) void bwd_prep_kernel(BwdArgs a) {
 __device__ inline int swz_perm(int c) { return (c & ~10) | ((c & 2) << 2) | ((c & 8) >> 2); }
 __device__ inline int swz_f(int r) { return (r & 8) | ((r & 3) << 1) | (((r >> 2) ^ (r >> 3)) & 1); }
 
-// Copy one 32 KB K or V^T tile of a page global -> LDS in that layout: copy i
-// of wave w fills LDS chunks [64*(4i + w), +64), i.e. row 16i + 4w + lane/16,
-// position lane%16.  The row's low four bits do not depend on i, so one
-// per-lane source offset serves all eight copies, with 2 KB steps on the
-// scalar base: a page keeps the 16-byte chunks 0..7 and 8..15 of every row in
-// two blocks of 128-byte rows, 16 KB apart.
+// Byte of 16-byte chunk c of row r of a 128-token page's K or V^T: chunks 0..7 and
+// 8..15 of every row are two blocks of 128-byte rows, 16 KB apart.
 __device__ inline uint32_t page_chunk(int r, int c) { return uint32_t((c >> 3) * 16384 + r * 128 + (c & 7) * 16); }
-__device__ inline uint32_t copy_offset_page(int wave, int lane) {
-  const int r = 4 * wave + (lane >> 4);
-  return page_chunk(r, swz_perm((lane & 15) ^ swz_f(r)));
-}
-__device__ inline void copy_tile_page(const uint8_t* src, uint32_t lds_tile, uint32_t voff, int wave) {
-#pragma unroll
-  for (int i = 0; i < 8; ++i) dma16(src + i * 2048, voff, lds_tile + uint32_t(wave) * 1024u + uint32_t(i) * 4096u);
-}
 
 // LDS byte offset of bf16 element (r, c) of a tile.
 __device__ inline uint32_t swz_elem(int r, int c) {
   return uint32_t(r * 256 + ((swz_perm(c >> 3) ^ swz_f(r & 15)) << 4) + (c & 7) * 2);
-}
-
-__device__ inline bf16x8 lds8(const uint8_t* base, uint32_t off) {
-  return as_bf16x8(*reinterpret_cast<const uint4*>(base + off));
 }
 
 // MFMA operand (A or B: lane l holds row/column l%32 and k-slots 8*(l/32)+e)
@@ -143,16 +128,6 @@ __device__ inline bf16x8 tr_operand(const lds_u8* tile, int col0, int lane, KRow
       (lds_v4i16*)(tile + swz_elem(krow(8 * hl + 4 + (rp >> 2)), c)));
   const v4i16 v[2] = {lo, hi};
   return __builtin_bit_cast(bf16x8, v);
-}
-
-// bf16 B operand for k-step kk (16 rows of a 32-row MFMA result block) from
-// the fp32 result registers: rows 16kk + 8j + 4hl + i, j in {0, 1}, i in 0..3,
-// i.e. k-slot kappa holds result row 16kk + swap23(kappa).
-__device__ inline bf16x8 rows_to_operand(const f32x16& x, int kk) {
-  bf16x8 r;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) r[e] = (__bf16)x[8 * kk + e];
-  return r;
 }
 
 // Per-lane parts of operand addresses, computed once per kernel so that every
@@ -178,10 +153,19 @@ __device__ inline TrTable tr_table(int lane) {
     }
   return T;
 }
-__device__ inline bf16x8 tr_op(const lds_u8* tile, const TrTable& T, int R, int cb) {
-  const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(tile + R * 256 + T.t[0][cb]));
-  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(tile + R * 256 + T.t[1][cb]));
-  const v4i16 v[2] = {lo, hi};
+// LDS reads by byte address (an address of zero is an ordinary one).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+__device__ inline u32x4 lds_read16(uint32_t at) { return *(const lds_u32x4*)(uintptr_t)at; }
+__device__ inline f32x4 lds_read4f(uint32_t at) { return *(const lds_f32x4*)(uintptr_t)at; }
+__device__ inline v4i16 lds_read_tr(uint32_t at) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(uintptr_t)at);
+}
+// The operand, with the tile's LDS address added to the table.
+__device__ inline bf16x8 tr_op_at(const TrTable& T, int R, int cb) {
+  const v4i16 v[2] = {lds_read_tr(T.t[0][cb] + uint32_t(R * 256)), lds_read_tr(T.t[1][cb] + uint32_t(R * 256))};
   return __builtin_bit_cast(bf16x8, v);
 }
 // RowTable: 16-byte row reads of an A/B operand (lane holds row R + rl, rl = ln
@@ -198,9 +182,6 @@ __device__ inline RowTable row_table(int lane) {
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) U.u[ks] = swz_elem(rl, 16 * ks + 8 * hl);
   return U;
-}
-__device__ inline bf16x8 row_op(const uint8_t* tile, const RowTable& U, int R, int ks) {
-  return lds8(tile, uint32_t(R * 256) + U.u[ks]);
 }
 
 // ---------------------------------------------------------------- dkdv ----
@@ -279,21 +260,6 @@ __device__ __forceinline__ void meet() {
 __device__ inline void dma16_low(const void* base, uint32_t off, uint32_t lds, uint64_t mask) {
   asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
                : : "v"(off), "s"(base), "s"(lds), "s"(mask) : "memory");
-}
-
-// LDS reads by byte address (an address of zero is an ordinary one).
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
-typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
-__device__ inline u32x4 lds_read16(uint32_t at) { return *(const lds_u32x4*)(uintptr_t)at; }
-__device__ inline f32x4 lds_read4f(uint32_t at) { return *(const lds_f32x4*)(uintptr_t)at; }
-// tr_op with the tile's LDS address already in the table, R a multiple of 16
-__device__ inline bf16x8 tr_op_at(const TrTable& T, int R, int cb) {
-  const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(uintptr_t)(T.t[0][cb] + uint32_t(R * 256)));
-  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(uintptr_t)(T.t[1][cb] + uint32_t(R * 256)));
-  const v4i16 v[2] = {lo, hi};
-  return __builtin_bit_cast(bf16x8, v);
 }
 
 template <int T>
@@ -639,16 +605,47 @@ __global__ __launch_bounds__(4 * T, 2) void bwd_dkdv_kernel(BwdArgs a) {
 
 // ------------------------------------------------------------------ dq ----
 
-// One workgroup per query tile.  The S^T and dP^T result rows of key block kb
-// hold keys kb*32 + swap23(m) (m = result row), the order in which the V
-// operand arrives when read transposed from the page's V^T; K rows are read
-// in the same order.  dS^T as a B operand then holds natural key order.
-// Entries naming a tile outside the window count no key.
+// One workgroup of four waves per query tile, two workgroups per CU.  The row's
+// list is walked in units of 64 keys (half of a 128-token tile; a half without
+// a valid key gives none).  128-token tiles: wave w holds queries 32w .. and
+// takes both 32-key blocks of a unit.  64-token tiles: wave w holds queries
+// 32 (w % 2) .. and takes key block w / 2; the two key blocks' dQ are added
+// through LDS at the end.
+//
+// Per key block: S^T = K Q^T, dP^T = V dO^T, dS^T, dQ^T += K^T dS^T.  The S^T and
+// dP^T result rows of a block hold keys swap23(m) of it (m = result row), the
+// order in which the V operand arrives when read transposed from the page's
+// V^T; K rows are read in the same order.  dS^T as a B operand then holds natural
+// key order.
+//
+// A unit is 32 KB of LDS, in 128-byte rows: K as two blocks of 64 dimensions
+// ([2][64 keys][64]), V^T as [128 dimensions][64 keys].  16-byte chunk c of K row
+// r sits at position c ^ f(r), f = (r1, r2 ^ r0, r3); of V^T row r at
+// c ^ 2 (r % 4).  Row reads (f runs through all eight values over the rows of
+// equal parity of any sixteen, and over rows 0..3 and 8..11) and transposing
+// reads (four consecutive rows, 64 bytes each) are free of bank conflicts, with
+// 32 or 64 banks, and a lane needs four addresses for K rows, four for K^T and
+// one per key block for V: the rest are compile-time offsets.
+//
+// What bounds it: three products per pair on the matrix cores, under the power
+// limit.  A whole page per step, copied into the only buffer between two
+// barriers, left a workgroup without work for the length of a copy; now the
+// next unit is copied, between the products, while one is used, one barrier per
+// unit, with the order of products, reads ahead and vector work written out as
+// in dkdv.  1K window: 13.8 -> 12.3 ms, the matrix cores busy 76 % of the cycles
+// at 1.55 GHz (58 % at 1.81 before).  64-token tiles had two waves a workgroup
+// and one per SIMD; with four and the keys shared 160 -> 80 us (batch 2, 6 heads,
+// 1,531 tokens, three chunks).
+constexpr int kDqList = 1024;                  // list entries taken into LDS at a time
+
+__device__ inline int swz_k(int r) { return ((r & 2) << 1) | (((r >> 1) ^ (r << 1)) & 2) | ((r >> 3) & 1); }
+
 template <int T>
-__global__ __launch_bounds__(2 * T, 2) void bwd_dq_kernel(BwdArgs a) {
-  // K rows and V^T of one page in the swizzled 256-byte-row layout (64 KB;
-  // a 64-token page fills K's first 64 rows and V^T's first 64 columns)
-  __shared__ uint4 sK[kT * 16], sV[kD * 16];
+__global__ __launch_bounds__(256, 2) void bwd_dq_kernel(BwdArgs a) {
+  constexpr int NB = T / 64;                   // key blocks of a wave per unit
+  constexpr uint32_t kUnit = 32768;
+  __shared__ uint4 sbuf[2][kUnit / 16];        // K 16 KB, V^T 16 KB
+  __shared__ uint32_t sunit[2 * kDqList + 1];  // (key tile << 1) | half; the count last
 
   const int row = blockIdx.x;                  // (b*H + h)*NT + i
   const int i = row % a.NT;
@@ -656,24 +653,10 @@ __global__ __launch_bounds__(2 * T, 2) void bwd_dq_kernel(BwdArgs a) {
   const int h = bh % a.H, b = bh / a.H;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lane = tid & 63, hl = lane >> 5, ln = lane & 31;
-  // copy offsets: 128-token pages with four waves, one offset for every copy;
-  // 64-token pages with two waves, copy i of wave w filling rows
-  // 8i + 4w + lane/16, whose low four bits depend on i % 2
-  uint32_t voff = 0, koff64[2] = {0, 0}, voff64[2] = {0, 0};
-  if constexpr (T == 128) {
-    voff = copy_offset_page(wave, lane);
-  } else {
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int r = 4 * wave + (lane >> 4) + 8 * k;
-      koff64[k] = uint32_t(r * 256 + swz_perm((lane & 15) ^ swz_f(r)) * 16);
-      voff64[k] = uint32_t(r * 128 + (swz_perm((lane & 15) ^ swz_f(r)) & 7) * 16);
-    }
-  }
-  const int q = wave * 32 + ln;                 // this lane's query (result column)
-  const lds_u8* lk = (const lds_u8*)sK;
-  const lds_u8* lv = (const lds_u8*)sV;
+  const int lane = tid & 63, hl = lane >> 5, ln = lane & 31, rp = lane & 15, g = (lane >> 4) & 1;
+  const int qw = T == 128 ? wave : wave & 1;   // query block
+  const int kw = T == 128 ? 0 : wave >> 1;     // first key block
+  const int q = qw * 32 + ln;                  // this lane's query (result column)
 
   const uint8_t* rec = a.work + size_t(row) * kBwdQTile;
   bf16x8 qf[8], of[8];
@@ -682,99 +665,246 @@ __global__ __launch_bounds__(2 * T, 2) void bwd_dq_kernel(BwdArgs a) {
     qf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(rec + size_t(q) * 256 + (2 * ks + hl) * 16));
     of[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(rec + kTile + size_t(q) * 256 + (2 * ks + hl) * 16));
   }
-  // per-lane query terms as MFMA seeds: S^T - LSE/scale and dP^T - delta
-  const float nl = reinterpret_cast<const float*>(rec + 2 * kTile)[q];
+  const float c2 = a.scale_log2;
+  // the lane's query terms: P = exp2(c2 S - LSE log2(e)) (-inf on padding
+  // queries), and -delta as the seed of the dP products
+  const float nl = reinterpret_cast<const float*>(rec + 2 * kTile)[q] * c2;
   const float nd = reinterpret_cast<const float*>(rec + 2 * kTile)[kT + q];
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-  f32x16 negl, negd;
+  f32x16 negd;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    negl[r] = nl;
-    negd[r] = nd;
+  for (int r = 0; r < 16; ++r) negd[r] = nd;
+
+  // operand addresses in the current buffer
+  const uint32_t lds0 = lds_addr(&sbuf[0][0]);
+  uint32_t kr[4], kt[2][2], vt[NB];
+  {
+    const int rr = swap23(ln);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      kr[k] = lds0 + uint32_t(kw * 4096 + rr * 128 + 16 * ((2 * k + hl) ^ swz_k(rr & 15)));
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        const int r = 8 * hl + 4 * hh + (rp >> 2);
+        kt[hh][m] = lds0 + uint32_t(kw * 4096 + r * 128 + 16 * ((4 * m + 2 * g + ((rp >> 1) & 1)) ^ swz_k(r)) + 8 * (rp & 1));
+      }
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+      vt[n] = lds0 + uint32_t(16384 + (8 * hl + (rp >> 2)) * 128 +
+                              16 * ((4 * (kw + n) + 2 * g + ((rp >> 1) & 1)) ^ (2 * (rp >> 2))) + 8 * (rp & 1));
   }
-  const TrTable TT = tr_table<false>(lane);    // K^T and V reads: k-slot kappa = row R + kappa
-  const RowTable RT = row_table<true>(lane);   // K rows kb*32 + swap23(ln)
+  // Copies: copy t of wave w for K fills block t/2, rows 8 (w + 4 (t%2)) + lane/8;
+  // for V^T rows 8 (w + 4t) + lane/8.
+  constexpr uint32_t kRowStep = T == 128 ? 128 : 256, kBlock = T == 128 ? 16384 : 128;
+  const uint32_t koff = uint32_t((lane >> 3) * kRowStep + 16 * ((lane & 7) ^ swz_k(8 * (wave & 1) + (lane >> 3))));
+  const uint32_t voff = uint32_t((lane >> 3) * 128 + 16 * ((lane & 7) ^ (2 * ((lane >> 3) & 3))));
+  const size_t pbytes = page_bytes(T, kD);
+  const uint8_t* head_pages = uniform_ptr(a.pool + size_t(bh) * a.NT * pbytes);
+  const size_t slot_stride = size_t(a.B) * a.H * a.NT * pbytes;
+  const int N = ((const const_i32*)a.counts)[row];
+  const int32_t* list = a.idx + size_t(row) * a.nk_cap;
 
   f32x16 dqt[4];                                // [4 dim blocks][32 dims x 32 queries]
 #pragma unroll
   for (int mb = 0; mb < 4; ++mb) dqt[mb] = f32x16{};
-  const float c2 = a.scale_log2;
-  const int N = ((const const_i32*)a.counts)[row];
-  const const_i32* list = ((const const_i32*)a.idx) + size_t(row) * a.nk_cap;
-  const size_t pbytes = page_bytes(T, kD);
-  const uint8_t* head_pages = a.pool + size_t(bh) * a.NT * pbytes;
-  const size_t slot_stride = size_t(a.B) * a.H * a.NT * pbytes;
 
-  for (int n = 0; n < N; ++n) {
-    const int j = list[n];
-    int kvalid = 0;
-    const uint8_t* page = head_pages + size_t(a.slot_of[0]) * slot_stride;
-    if (unsigned(j) < unsigned(a.nk)) {
-      const int pos = j / a.NT, t = j - pos * a.NT;
-      kvalid = tile_valid(a.tv, t, a.NT, a.tail, T);
-      page = head_pages + size_t(a.slot_of[pos]) * slot_stride + size_t(t) * pbytes;
+  struct Unit {
+    const uint8_t* k;      // its K rows
+    const uint8_t* v;      // and V^T rows
+    int valid;             // valid keys
+  };
+  auto unit = [&](uint32_t x) {
+    const int half = int(x & 1u);
+    const int pos = div_nt(x >> 1, a.nt_div);
+    const int t = int(x >> 1) - pos * a.NT;
+    const uint8_t* page = head_pages + size_t(a.slot_of[pos]) * slot_stride + size_t(t) * pbytes;
+    return Unit{page + half * 64 * kRowStep, page + T * kD * 2 + 16384 * half,
+                min(tile_valid(a.tv, t, a.NT, a.tail, T) - 64 * half, 64)};
+  };
+  auto issue = [&](const Unit& u, uint32_t buf, int k) {
+    const int t = k & 3;
+    const uint32_t dst = lds0 + buf * kUnit + uint32_t(wave) * 1024u;
+    if (k < 4)
+      dma16(u.k + (t >> 1) * kBlock + uint32_t(8 * (wave + 4 * (t & 1))) * kRowStep, koff, dst + uint32_t(t) * 4096u);
+    else
+      dma16(u.v + uint32_t(wave + 4 * t) * 1024u, voff, dst + 16384u + uint32_t(t) * 4096u);
+  };
+  auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
+
+  // Products of a unit: per key block n S (0..7), dP (8..15); then per block dQ.
+  // With two blocks: S0, dP0, S1, dP1, dQ0, dQ1.
+  constexpr int kAll = 24 * NB, kSP = 16 * NB;
+  constexpr int kReads = 5;                     // operands in flight: what the registers hold
+  auto load = [&](int k) -> bf16x8 {
+    if (k < kSP) {
+      const int n = k >> 4, ks = k & 7;
+      if ((k & 8) == 0)
+        return __builtin_bit_cast(bf16x8, lds_read16(kr[ks & 3] + uint32_t(n * 4096 + (ks >> 2) * 8192)));
+      const v4i16 v[2] = {lds_read_tr(vt[n] + uint32_t(ks * 2048)), lds_read_tr(vt[n] + uint32_t(ks * 2048 + 512))};
+      return __builtin_bit_cast(bf16x8, v);
     }
-    __syncthreads();                            // previous tile consumed
-    if constexpr (T == 128) {
-      copy_tile_page(page, lds_addr(sK), voff, wave);
-      copy_tile_page(page + kTile, lds_addr(sV), voff, wave);
-    } else {
-      // K: 64 rows of 256 bytes, 8 copies; V^T: 128 rows of 128 bytes, 16 copies
-      const uint32_t lk0 = lds_addr(sK) + uint32_t(wave) * 1024u, lv0 = lds_addr(sV) + uint32_t(wave) * 1024u;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) dma16(page + (c >> 1) * 4096, koff64[c & 1], lk0 + uint32_t(c) * 2048u);
-#pragma unroll
-      for (int c = 0; c < 16; ++c)
-        dma16(page + T * kD * 2 + (c >> 1) * 2048, voff64[c & 1], lv0 + uint32_t(c) * 2048u);
-    }
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-    __syncthreads();
-#pragma unroll
-    for (int kb = 0; kb < T / 32; ++kb) {
-      // S^T = K Q^T and dP^T = V dO^T: A operands are K rows kb*32 + swap23(ln)
-      // and V read transposed from V^T (tile row = dim, columns kb*32 ..);
-      f32x16 sv, dpv;
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_op((const uint8_t*)sK, RT, kb * 32, ks), qf[ks],
-                                                     ks ? sv : negl, 0, 0, 0);
-        dpv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_op(lv, TT, 16 * ks, kb), of[ks], ks ? dpv : negd, 0, 0, 0);
-      }
-      // keys past the tile's valid rows get -inf, so their weights vanish (a
-      // rare case: the key indices are formed here, not held across the loop)
-      if (kvalid < T) {
+    const int m = k - kSP, n = m >> 3, kk = (m >> 2) & 1, mb = m & 3;
+    const uint32_t at = uint32_t(n * 4096 + kk * 2048 + (mb >> 1) * 8192);
+    const v4i16 v[2] = {lds_read_tr(kt[0][mb & 1] + at), lds_read_tr(kt[1][mb & 1] + at)};
+    return __builtin_bit_cast(bf16x8, v);
+  };
+  auto body = [&](const Unit& cur, const Unit& next, uint32_t nbuf) {
+    f32x16 sv[NB], dp[NB];
+    bf16x8 op[NB][2], x[kAll];
+    // keys past the unit's valid ones weigh nothing (a rare case: their indices
+    // are formed here, not held across the loop)
+    auto mask = [&](int n) {
+      if (cur.valid < 64) {
         int h4 = 4 * hl;
         asm volatile("" : "+v"(h4));
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          if (kb * 32 + swap23(8 * (r >> 2) + h4 + (r & 3)) >= kvalid) sv[r] = -INFINITY;
+          if ((kw + n) * 32 + swap23(8 * (r >> 2) + h4 + (r & 3)) >= cur.valid) sv[n][r] = -INFINITY;
       }
-      // result row m = 8*(r/4) + 4*hl + r%4 holds key kb*32 + swap23(m)
-      f32x16 ds;
+    };
+    auto weight = [&](int n, int r) { sv[n][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[n][r], c2, nl)); };
+    auto ds = [&](int n, int e) {
+      op[n][e >> 2][2 * (e & 3)] = (__bf16)(sv[n][2 * e] * dp[n][2 * e]);
+      op[n][e >> 2][2 * (e & 3) + 1] = (__bf16)(sv[n][2 * e + 1] * dp[n][2 * e + 1]);
+    };
 #pragma unroll
-      for (int r = 0; r < 16; ++r) ds[r] = __builtin_amdgcn_exp2f(sv[r] * c2) * dpv[r];
-      // dQ^T += K^T dS^T: k-slot kappa of step kk = key kb*32 + 16kk + kappa
+    for (int k = 0; k < kReads; ++k) x[k] = load(k);
+    fence();
+    auto eight = [&](auto first) {              // products first .. first + 7
+      constexpr int k0 = decltype(first)::value;
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        const bf16x8 db = rows_to_operand(ds, kk);
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-          dqt[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_op(lk, TT, kb * 32 + 16 * kk, mb), db, dqt[mb], 0, 0, 0);
+      for (int j = 0; j < 8; ++j) {
+        const int k = k0 + j;
+        if constexpr (k0 < kSP) {
+          const int n = k0 >> 4;
+          if constexpr ((k0 & 8) == 0)
+            sv[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[k], qf[j], j ? sv[n] : f32x16{}, 0, 0, 0);
+          else
+            dp[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[k], of[j], j ? dp[n] : negd, 0, 0, 0);
+        } else {
+          dqt[j & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[k], op[(k0 - kSP) >> 3][j >> 2], dqt[j & 3], 0, 0, 0);
+        }
+        if (k + kReads < kAll) x[k + kReads] = load(k + kReads);
+        if constexpr (k0 < kSP && (k0 & 8) != 0) {   // beside dP of a block: its weights
+          weight(k0 >> 4, 2 * j);
+          weight(k0 >> 4, 2 * j + 1);
+        }
+        if constexpr (NB == 2 && k0 == 16) ds(0, j);   // beside S of block 1
+        if constexpr (NB == 2 && k0 == 32) ds(1, j);   // beside dQ of block 0
+        if (k % 2 == 1 && k < 16) issue(next, nbuf, k >> 1);   // the next unit's copies
+        fence();
       }
+      // what was formed here stays here (the masks' branches would let the
+      // compiler sink it to where it is used)
+      if constexpr (k0 < kSP && (k0 & 8) != 0) asm volatile("" : "+v"(sv[k0 >> 4]));
+      if constexpr (NB == 2 && k0 == 16) asm volatile("" : "+v"(op[0][0]), "+v"(op[0][1]));
+    };
+    eight(std::integral_constant<int, 0>{});
+    mask(0);
+    eight(std::integral_constant<int, 8>{});
+    if constexpr (NB == 2) {
+      eight(std::integral_constant<int, 16>{});
+      mask(1);
+      eight(std::integral_constant<int, 24>{});
+      eight(std::integral_constant<int, 32>{});
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ds(0, e);
+    }
+    eight(std::integral_constant<int, kAll - 8>{});
+  };
+
+  for (int base = 0; base < N; base += kDqList) {
+    // the units of the next kDqList entries; entries naming a tile outside the
+    // window (stale lists) count no key
+    if (base > 0) meet<0>();                    // the table is no longer read
+    if (wave == 0) {
+      int cnt = 0;
+      const int end = min(N, base + kDqList);
+      for (int e0 = base; e0 < end; e0 += 256) {
+        uint32_t jj[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int e = e0 + 64 * k + lane;
+          jj[k] = e < end ? uint32_t(list[e]) : 0xffffffffu;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t j = jj[k];
+          int n = 0;
+          if (j < uint32_t(a.nk)) {
+            const int v = tile_valid(a.tv, int(j % uint32_t(a.NT)), a.NT, a.tail, T);
+            n = v > 64 ? 2 : (v > 0 ? 1 : 0);
+          }
+          const uint64_t b1 = __ballot(n >= 1), b2 = __ballot(n == 2);
+          const uint64_t below = (uint64_t(1) << lane) - 1;
+          const int at = cnt + __popcll(b1 & below) + __popcll(b2 & below);
+          if (n >= 1) sunit[at] = j << 1;
+          if (n == 2) sunit[at + 1] = (j << 1) | 1u;
+          cnt += __popcll(b1) + __popcll(b2);
+        }
+      }
+      if (lane == 0) sunit[2 * kDqList] = uint32_t(cnt);
+    }
+    meet<0>();
+    const int U = __builtin_amdgcn_readfirstlane(sunit[2 * kDqList]);
+    if (U == 0) continue;
+    auto entry = [&](int u) { return uint32_t(__builtin_amdgcn_readfirstlane(sunit[min(u, U - 1)])); };
+    Unit cur = unit(entry(0)), next = unit(entry(1));
+#pragma unroll
+    for (int k = 0; k < 8; ++k) issue(cur, 0, k);
+    for (int u = 0; u < U; ++u) {
+      meet<0>();                                // unit u has landed; the other buffer is free
+      const uint32_t x2 = sunit[min(u + 2, U - 1)];
+      body(cur, next, uint32_t(u + 1) & 1u);    // past the end the last unit is copied again, and not read
+      const uint32_t d = (u & 1) ? uint32_t(-int(kUnit)) : kUnit;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) kr[k] += d;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) kt[k >> 1][k & 1] += d;
+#pragma unroll
+      for (int k = 0; k < NB; ++k) vt[k] += d;
+      cur = next;
+      next = unit(__builtin_amdgcn_readfirstlane(x2));
+    }
+    if (U & 1) {                                // the next entries start in buffer 0 again
+#pragma unroll
+      for (int k = 0; k < 4; ++k) kr[k] -= kUnit;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) kt[k >> 1][k & 1] -= kUnit;
+#pragma unroll
+      for (int k = 0; k < NB; ++k) vt[k] -= kUnit;
     }
   }
+  meet<0>();                                    // no copy outlives the workgroup
 
-  // padding rows inside the chunk accumulated zeros (their seed is -inf)
+  if constexpr (T == 64) {
+    float* xo = reinterpret_cast<float*>(&sbuf[0][0]);   // [2 query blocks][4][16][64 lanes]
+    if (kw == 1) {
+#pragma unroll
+      for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) xo[((qw * 4 + mb) * 16 + e) * 64 + lane] = dqt[mb][e];
+    }
+    meet<0>();
+    if (kw == 1) return;
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) dqt[mb][e] += xo[((qw * 4 + mb) * 16 + e) * 64 + lane];
+  }
+  // padding rows inside the chunk accumulated zeros (their weights are zero)
   if (size_t(i) * T + q < size_t(a.L)) {
     const size_t base = ((size_t(b) * a.L + size_t(i) * T + q) * a.H + h) * kD;
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int d0 = mb * 32 + 8 * g + 4 * hl;
+      for (int k = 0; k < 4; ++k) {
+        const int d0 = mb * 32 + 8 * k + 4 * hl;
         *reinterpret_cast<float4*>(a.dq + base + d0) =
-            make_float4(dqt[mb][4 * g] * a.scale, dqt[mb][4 * g + 1] * a.scale, dqt[mb][4 * g + 2] * a.scale,
-                        dqt[mb][4 * g + 3] * a.scale);
+            make_float4(dqt[mb][4 * k] * a.scale, dqt[mb][4 * k + 1] * a.scale, dqt[mb][4 * k + 2] * a.scale,
+                        dqt[mb][4 * k + 3] * a.scale);
       }
   }
 }
@@ -842,7 +972,7 @@ hipError_t launch_bwd_t(const BwdArgs& a, hipStream_t stream) {
   if (e != hipSuccess) return e;
   bwd_dkdv_kernel<T><<<ktiles, 4 * T, 0, stream>>>(a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  bwd_dq_kernel<T><<<qrows, 2 * T, 0, stream>>>(a);
+  bwd_dq_kernel<T><<<qrows, 256, 0, stream>>>(a);
   return hipGetLastError();
 }
 

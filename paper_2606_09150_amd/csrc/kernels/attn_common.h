@@ -41,6 +41,27 @@ __device__ inline void dma16(const void* base, uint32_t off, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds) : "memory");
 }
 
+// j / NT for 0 <= j < 2^31 from d = (2^64 - 1) / NT: ((j + 1) * d) >> 64 in
+// scalar integer arithmetic (a division by a run-time value would otherwise
+// use vector float instructions in the softmax waves).  With d = (2^64 - r) / NT,
+// 0 < r <= NT, the product is (j + 1) / NT minus less than 2^-32, which floors
+// to j / NT.
+__device__ __forceinline__ int div_nt(uint32_t j, uint64_t d) {
+  const uint64_t x = uint64_t(j) + 1u;
+  const uint64_t lo = x * uint32_t(d);
+  const uint64_t hi = x * uint32_t(d >> 32);
+  return int((hi + (lo >> 32)) >> 32);
+}
+
+// A pointer that is the same on every lane, held in scalar registers.
+__device__ __forceinline__ const uint8_t* uniform_ptr(const uint8_t* q) {
+  const uint64_t p = reinterpret_cast<uint64_t>(q);
+  // (the builtin returns int: widen through uint32_t, not by sign extension)
+  const uint64_t lo = uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(p)));
+  const uint64_t hi = uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(p >> 32)));
+  return reinterpret_cast<const uint8_t*>(lo | (hi << 32));
+}
+
 // s_waitcnt immediates (gfx9 encoding): vmcnt in [3:0] and [15:14], expcnt
 // in [6:4], lgkmcnt in [11:8].
 constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }

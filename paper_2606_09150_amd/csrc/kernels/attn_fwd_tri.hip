@@ -142,26 +142,6 @@ struct HalfCopy {
   uint32_t step;    // source bytes per c/8: the next K block (16384) or the next 64 rows of V^T (8192)
   bool on;
 };
-// j / NT for 0 <= j < 2^31 from d = (2^64 - 1) / NT: ((j + 1) * d) >> 64 in
-// scalar integer arithmetic (a division by a run-time value would otherwise
-// use vector float instructions in the softmax waves).  With d = (2^64 - r) / NT,
-// 0 < r <= NT, the product is (j + 1) / NT minus less than 2^-32, which floors
-// to j / NT.
-__device__ __forceinline__ int div_nt(uint32_t j, uint64_t d) {
-  const uint64_t x = uint64_t(j) + 1u;
-  const uint64_t lo = x * uint32_t(d);
-  const uint64_t hi = x * uint32_t(d >> 32);
-  return int((hi + (lo >> 32)) >> 32);
-}
-
-// A pointer that is the same on every lane, held in scalar registers.
-__device__ __forceinline__ const uint8_t* uniform_ptr(const uint8_t* q) {
-  const uint64_t p = reinterpret_cast<uint64_t>(q);
-  // (the builtin returns int: widen through uint32_t, not by sign extension)
-  const uint64_t lo = uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(p)));
-  const uint64_t hi = uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(p >> 32)));
-  return reinterpret_cast<const uint8_t*>(lo | (hi << 32));
-}
 __device__ __forceinline__ void half_copy(const HalfCopy& cp, uint32_t lane_off, int t) {
   dma16(uniform_ptr(cp.src + 4096 * (t & 1) + cp.step * (t >> 1)), lane_off, cp.lds + 4096u * uint32_t(t));
 }

@@ -24,6 +24,7 @@ struct BwdArgs {
   float* dv;              // [n_live][B, L, H, D]
   uint8_t* work;
   int32_t B, H, L, T, NT, tail, nk, nk_cap, mask_words, n_live;
+  uint64_t nt_div;        // as in AttnArgs
   float scale, scale_log2;
   int32_t slot_of[UF_MAX_CHUNKS];
   TileValid tv;

@@ -599,6 +599,7 @@ int bwd_args(const uf_kv* kv, const void* d_q, const void* d_o, const void* d_do
   a.nk_cap = f.nk_cap;
   a.mask_words = int32_t(lay.mask_words);
   a.n_live = int32_t(kv->live.size());
+  a.nt_div = f.nt_div;
   a.scale = f.scale;
   a.scale_log2 = f.scale_log2;
   for (int p = 0; p < a.n_live; ++p) a.slot_of[p] = f.slot_of[p];

@@ -129,6 +129,25 @@ def test_backward_half_tile_units(T, L, p):
     assert max(worst) <= GRAD_TOL, worst
 
 
+# The query-side kernel takes a row's list into LDS 1,024 entries at a time: lists
+# of 1,024 to 1,088 tiles (64 chunks), an odd number of units in the first part.
+@pytest.mark.parametrize("T,L,p", [(64, 1025, 1.0), (128, 2049, 1.0), (128, 1985, 1.0), (64, 1088, 0.95)])
+def test_backward_long_lists(T, L, p):
+    P = require_gpu()
+    log(f"bwd long lists T={T} L={L} p={p}")
+    case = Case(P, 1, L, 1, T, 64, True, seed=2450 + L, gen_device="cuda")
+    for _ in range(64):
+        case.append()
+    rule = case.rule(p)
+    q, _, _, do, dq, _, _ = _run(case, rule)
+    rows = [0, 31, 32, T - 1, T, L // 2, L - 2, L - 1]
+    want = oracle.sparse_causal_attention_bwd_rows(case.ring, case._host(q), case._host(do), case.oracle_bits(rule), T,
+                                                   1 / math.sqrt(128), [(0, 0, r) for r in rows])
+    err = _rows(dq.cpu().numpy()[0, rows, 0], want)
+    log(f"  sampled dq rows worst per-row={err:.3e}")
+    assert err <= GRAD_TOL
+
+
 def test_backward_tiny_workload():
     """The tiny window (64-token tiles, 2 heads, 384 keys, every tile kept) in full."""
     P = require_gpu()
