@@ -245,17 +245,6 @@ __device__ inline void copy_tile8_page(const uint8_t* src, uint32_t lds_tile, ui
   for (int i = 0; i < 4; ++i) dma16(src + i * 4096, voff, lds_tile + uint32_t(wave) * 1024u + uint32_t(i) * 8192u);
 }
 
-// s_waitcnt vmcnt(N) lgkmcnt(0), then the workgroup barrier; the signal fences
-// keep the compiler from moving LDS accesses across it.
-template <int N>
-__device__ __forceinline__ void meet() {
-  constexpr int imm = (N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14);
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_s_waitcnt(imm);
-  __builtin_amdgcn_s_barrier();
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
 // dma16 of the lanes in `mask` only (the whole wave is active around it).
 __device__ inline void dma16_low(const void* base, uint32_t off, uint32_t lds, uint64_t mask) {
   asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"

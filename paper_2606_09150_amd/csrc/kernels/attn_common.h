@@ -7,7 +7,6 @@ namespace uf {
 namespace attn {
 
 constexpr int kD = 128;
-constexpr float kLazyLog2 = 8.0f;   // raise the running max only when it grows by more than 2^8
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -65,7 +64,24 @@ __device__ __forceinline__ const uint8_t* uniform_ptr(const uint8_t* q) {
 // s_waitcnt immediates (gfx9 encoding): vmcnt in [3:0] and [15:14], expcnt
 // in [6:4], lgkmcnt in [11:8].
 constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
-constexpr int kWaitLgkm0 = 15 | (7 << 4) | (0 << 8) | (3 << 14);
+
+// s_waitcnt vmcnt(N) lgkmcnt(0), then the workgroup barrier; the signal fences
+// keep the compiler from moving LDS accesses across it.
+template <int N>
+__device__ __forceinline__ void meet() {
+  constexpr int imm = (N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14);
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(imm);
+  __builtin_amdgcn_s_barrier();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+// 3-bit XOR pattern of LDS row r (r % 16): bijective in bits 0..2 for either
+// value of bit 3, and in bits 1..3 for either value of bit 0.
+__device__ __forceinline__ int swz(int r) {
+  const int b3 = (r >> 3) & 1;
+  return ((((r >> 2) & 1) ^ b3) << 2) | (r & 2) | ((r & 1) ^ b3);
+}
 
 __device__ inline uint32_t lds_addr(const void* p) {
   return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)p);

@@ -5,35 +5,40 @@
 // list (Eq. 4: attention restricted to the kept blocks of the chunk-causal
 // window) and keeps an online softmax.
 //
-// Work split: four waves, two key groups of two.  Wave (g, w) holds queries
-// 32w .. 32w+31 of the tile and walks list entries g, g + 2, g + 4, ...; each
-// group keeps its own (m, l, O), and at the end group 1 hands its state to
-// group 0 through LDS (log-sum-exp merge).  A row's walk is a chain of
-// dependent steps (copy, S, softmax, PV) with one wave per SIMD, so two groups
-// halve its length.  The kernel computes S^T = K Q^T with
-// v_mfma_f32_32x32x16_bf16 (K from LDS as the A operand, Q held in registers as
-// the B operand), so in the result layout every lane owns one query column and
-// 16 key rows per 32-key block; the row max and row sum need one exchange with
-// the partner lane (permlane32 swap).  The exponentiated scores are rounded to
-// bf16 in place and reused directly as the B operand of O^T += V^T P^T; V pages
-// are stored transposed with the keys of each group of 16 in swap23 order,
-// which is exactly the k-slot order in which the S^T result lanes hold them.
+// Work split: four waves, three workgroups per CU.  Wave (kw, qw) holds queries
+// 32 qw .. of the tile and takes key block kw (32 keys) of every kept tile; the
+// two key blocks keep their own (m, l, O), and at the end block 1 hands its
+// state to block 0 through LDS (log-sum-exp merge).  S^T = K Q^T and
+// O^T += V^T P^T on v_mfma_f32_32x32x16_bf16, K and V^T from LDS as the A operand,
+// Q^T and P^T in registers as the B operand: every lane owns one query column, so
+// the row max and sum need one permlane32 exchange, and the weights rounded to
+// bf16 in place are the PV operand (V pages keep the keys of each group of 16 in
+// swap23 order, the k-slot order of the S^T result lanes).
 //
-// Memory pipeline: pages are copied HBM -> LDS by direct global_load_lds
-// (16 bytes per lane, no register staging) into one K buffer and one V buffer
-// per group with an XOR swizzle of 16-byte chunks (conflict-free MFMA operand
-// reads).  A group requests K of its next tile as soon as every wave has read
-// the current K (so it lands during softmax and PV), and V of its next tile as
-// soon as every wave has read the current V (so it lands during the next S).
-// Both groups run the same number of steps (a group without a tile in a step
-// idles through it), so the workgroup barriers that publish the copies match.
+// What bounds it: a 64-token tile brings 32 KB of K and V for half the products
+// of a 128-token one, so the copies (64 bytes a cycle and CU if the matrix cores
+// never waited) and their latency.  Per tile a workgroup runs S, softmax and PV
+// one after the other and waits for copies twice; three workgroups beside each
+// other, 48 KB of LDS each (two K buffers, one V buffer), fill each other's
+// waits: 12 heads, 4,665 tokens, four chunks, half of two of them kept, take
+// 477 us (840 TFLOP/s); one workgroup per CU whose two groups of two waves walked
+// alternate tiles in single buffers, one wave per SIMD, took 855 us (469).  The
+// smallest window (6 rows of 6 tiles) takes 9.9 us, 12.1 before.
 //
-// Softmax runs in base 2 with scale*log2(e) folded into one FMA.  The running
-// max is raised lazily: O and l are rescaled only when some lane's tile max
-// exceeds its running max by more than 8 (base-2 units), so exponentials stay
-// <= 2^8 and the rescale is rare.  Row sums add the bf16-rounded weights that
-// the PV product uses (v_dot2_f32_bf16).  O is normalised once at the end and
-// rounded to bf16 (nearest even).
+// Memory: pages are copied HBM -> LDS by direct global_load_lds (16 bytes per
+// lane).  K lies in LDS as two blocks of 64 dimensions, V^T as one of 64 keys,
+// all in 128-byte rows whose 16-byte chunks are XOR-swizzled as in the 128-token
+// kernel, so that an operand read needs one of four lane addresses plus a
+// compile-time offset and is free of bank conflicts.  K of the next tile and V
+// of this one are requested when S begins (every wave has then finished with
+// both buffers); V is waited for before PV, K before the next S.
+//
+// Softmax in base 2 with a lazy offset m per lane: weights exp2(c2 s - m), c2 =
+// scale*log2(e).  The offset is raised, and O and l rescaled, only when a lane's
+// 16 weights sum to more than kSumBound or on its first valid key.  The row sum
+// adds the bf16-rounded weights that the PV product uses (v_dot2_f32_bf16; fp32
+// adds of the unrounded ones were 0.6 % faster and raised O's error by 1 to 3 %).
+// O is normalised once at the end and rounded to bf16 (nearest even).
 #include "attn_common.h"
 
 namespace uf {
@@ -41,39 +46,26 @@ namespace {
 
 using namespace attn;
 
-// With one wave per SIMD nothing hides an operand read's LDS latency but the
-// wave's own MFMAs: keep kAhead reads in flight, then one read per MFMA.
-template <int kReads>
-__device__ inline void schedule_reads_ahead() {
-  constexpr int kAhead = 8;
-  __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
-#pragma unroll
-  for (int i = 0; i < kReads - kAhead; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-  }
-  __builtin_amdgcn_sched_group_barrier(0x008, kAhead, 0);
+constexpr int kT = 64;
+constexpr uint32_t kBuf = 16384;       // a tile's K, or its V^T
+constexpr float kSumBound = 4096.0f;   // lane row-sum bound of 16 weights
+constexpr int kList = 1024;            // list entries taken into LDS at a time
+constexpr int kAhead = 6;              // operands in flight ahead of their product
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+__device__ inline bf16x8 lds_operand(uint32_t at) {
+  return __builtin_bit_cast(bf16x8, *(const lds_u32x4*)(uintptr_t)at);
 }
 
 // SPLIT: as in the 128-token kernel, the first a.split_from workgroups run
 // rows 0 .. split_from-1 whole and every later row is cut into a.split slices
 // of its list; a slice writes its unnormalised O, its offset (base-2 units)
 // and its row sum to a.work for the merge.
-template <int T, bool SPLIT>
-__global__ __launch_bounds__(T * 4, 1) void attn_fwd_kernel(AttnArgs a) {
-  constexpr int kQW = T / 32;                      // query blocks (waves) of a group
-  constexpr int kGroups = 2;                       // key groups
-  constexpr int kGThreads = kQW * 64;              // threads of a group
-  constexpr int KB = T / 32;                       // 32-key blocks per key tile
-  constexpr int kKC = kD / 8;                      // 16-byte chunks per K row
-  constexpr int kVC = T / 8;                       // 16-byte chunks per V^T row
-  constexpr int kKLoads = T * kKC / kGThreads;     // direct loads per lane for a K tile
-  constexpr int kVLoads = kD * kVC / kGThreads;    // and for a V tile
-  static_assert(kKLoads == 8 && kVLoads == 8, "load split");
-  __shared__ uint4 sK[kGroups][T * kKC];
-  __shared__ uint4 sV[kGroups][kD * kVC];
-  __shared__ float sML[kQW][2][64];                // group 1's (m, l) for the merge
-  static_assert(sizeof(sK) >= size_t(kQW) * 4 * 16 * 64 * 4, "group 1's O fits the K buffers");
+template <bool SPLIT>
+__global__ __launch_bounds__(256, 3) void attn_fwd_kernel(AttnArgs a) {
+  __shared__ uint4 sbuf[3][kBuf / 16];             // K, K, V^T
+  __shared__ uint32_t sunit[kList + 1];            // key tiles with a valid key; the count last
 
   int row = int(blockIdx.x), part = 0;
   bool partial = false;
@@ -89,249 +81,232 @@ __global__ __launch_bounds__(T * 4, 1) void attn_fwd_kernel(AttnArgs a) {
   const int b = bh / a.H;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int qw = wave % kQW;                       // query block
-  const int grp = wave / kQW;                      // key group
+  const int qw = wave & 1;                         // query block
+  const int kw = wave >> 1;                        // key block
   const int lane = tid & 63;
-  const int g = lane >> 5;
+  const int hl = lane >> 5;
   const int ln = lane & 31;
-  const int qrow = qt * T + qw * 32 + ln;
+  const int qrow = qt * kT + qw * 32 + ln;
   const bool qvalid = qrow < a.L;
 
-  // Q^T as the B operand: lane holds query ln, dims 16*ks + 8*g .. +8.
-  bf16x8 qf[kD / 16];
+  // Q^T as the B operand: lane holds query ln, dims 16*ks + 8*hl .. +8.
+  bf16x8 qf[8];
   {
-    const uint16_t* qp = a.q + ((size_t(b) * a.L + (qvalid ? qrow : 0)) * a.H + h) * kD + 8 * g;
+    const uint16_t* qp = a.q + ((size_t(b) * a.L + (qvalid ? qrow : 0)) * a.H + h) * kD + 8 * hl;
 #pragma unroll
-    for (int ks = 0; ks < kD / 16; ++ks) {
+    for (int ks = 0; ks < 8; ++ks) {
       uint4 u = make_uint4(0, 0, 0, 0);
       if (qvalid) u = *reinterpret_cast<const uint4*>(qp + 16 * ks);
       qf[ks] = as_bf16x8(u);
     }
-    // Q is in registers before any page copy is issued, so that the only
-    // vector-memory operations in flight inside the loop are page copies.
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
   }
-
-  f32x16 o[kD / 32];
+  const uint32_t lds0 = lds_addr(&sbuf[0][0]);
+  uint32_t rk[4], rv[2];                           // K rows 32 kw + ln; V^T rows ln, keys 32 kw + 16 step ..
 #pragma unroll
-  for (int mb = 0; mb < kD / 32; ++mb) o[mb] = f32x16{};
-  float m = -INFINITY;   // running (lazily raised) max of raw scores q.k
-  float l = 0.f;         // running sum of bf16(exp2((s - m) * c2))
+  for (int j = 0; j < 4; ++j)
+    rk[j] = lds0 + uint32_t(4096 * kw + 128 * ln + 16 * ((2 * j + hl) ^ swz(ln & 15)));
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+    rv[s] = lds0 + 2 * kBuf + uint32_t(128 * ln + 16 * ((4 * kw + 2 * s + hl) ^ swz(ln & 15)));
+  // Copies: copy t of wave w for K fills block t/2, rows 8 (w + 4 (t%2)) + lane/8;
+  // for V^T rows 8 (w + 4t) + lane/8.
+  const uint32_t chunk = uint32_t(16 * ((lane & 7) ^ swz(8 * (wave & 1) + (lane >> 3))));
+  const uint32_t koff = uint32_t((lane >> 3) * 256) + chunk, voff = uint32_t((lane >> 3) * 128) + chunk;
 
+  const size_t pbytes = page_bytes(kT, kD);
+  const uint8_t* head_pages = uniform_ptr(a.pool + (size_t(b) * a.H + h) * a.NT * pbytes);
+  const size_t slot_stride = size_t(a.B) * a.H * a.NT * pbytes;
   const int total = ((const const_i32*)a.counts)[row];
   const int first = partial ? int(int64_t(part) * total / a.split) : 0;
   const int count = partial ? int(int64_t(part + 1) * total / a.split) - first : total;
-  const const_i32* list = (const const_i32*)a.idx + size_t(row) * a.nk_cap + first;
-  const size_t pbytes = page_bytes(T, kD);
-  const uint8_t* head_pages = a.pool + (size_t(b) * a.H + h) * a.NT * pbytes;
-  const size_t slot_stride = size_t(a.B) * a.H * a.NT * pbytes;
+  const int32_t* list = a.idx + size_t(row) * a.nk_cap + first;
   const float c2 = a.scale_log2;
-  const float lazy_raw = kLazyLog2 / fabsf(c2);
 
-  // Entries naming a tile outside the window (stale lists) are skipped: the
-  // group idles through that step.
-  auto usable = [&](int n) { return n < count && unsigned(list[n]) < unsigned(a.nk); };
-  auto page_of = [&](int n) {
-    const int j = list[n];
-    const int pos = j / a.NT;
-    const int t = j - pos * a.NT;
-    return head_pages + size_t(a.slot_of[pos]) * slot_stride + size_t(t) * pbytes;
+  f32x16 o[4];                                     // O^T [4 x 32 dims][32 queries]
+#pragma unroll
+  for (int mb = 0; mb < 4; ++mb) o[mb] = f32x16{};
+  float m = -INFINITY;                             // offset (base-2 units), -inf until the lane's first valid key
+  float moff = 0.f;                                // m, or 0 while m is -inf
+  float l = 0.f;                                   // this lane's share of the row sum
+
+  struct Unit {
+    const uint8_t* page;
+    int valid;
   };
-  // Direct HBM -> LDS copies into the group's buffers.  Instruction i of the
-  // group's wave w fills the 64 chunks [64*(i*kQW + w), +64) of a buffer; lane
-  // l of it fetches the page chunk that the XOR swizzle assigns to that LDS
-  // position.  The per-lane byte offsets are loop invariant.
-  uint32_t koff[kKLoads], voff[kVLoads];
-#pragma unroll
-  for (int i = 0; i < kKLoads; ++i) {
-    const int p = (i * kQW + qw) * 64 + lane;
-    const int r = p / kKC, c = p % kKC;
-    koff[i] = uint32_t(r * kKC + (c ^ (r & 15))) * 16u;
-  }
-#pragma unroll
-  for (int i = 0; i < kVLoads; ++i) {
-    const int p = (i * kQW + qw) * 64 + lane;
-    const int d = p / kVC, c = p % kVC;
-    voff[i] = uint32_t(d * kVC + (c ^ (d & (kVC - 1)))) * 16u;
-  }
-  const uint4* kbuf = sK[grp];
-  const uint4* vbuf = sV[grp];
-  const uint32_t k_lds = lds_addr(kbuf) + qw * 1024u;
-  const uint32_t v_lds = lds_addr(vbuf) + qw * 1024u;
-  auto issue_k = [&](const uint8_t* page) {
-#pragma unroll
-    for (int i = 0; i < kKLoads; ++i) dma16(page, koff[i], k_lds + uint32_t(i * kQW) * 1024u);
+  auto unit = [&](uint32_t j) {
+    const int pos = div_nt(j, a.nt_div);
+    const int t = int(j) - pos * a.NT;
+    return Unit{head_pages + size_t(a.slot_of[pos]) * slot_stride + size_t(t) * pbytes,
+                tile_valid(a.tv, t, a.NT, a.tail, kT)};
   };
-  auto issue_v = [&](const uint8_t* page) {
-    const uint8_t* vpage = page + size_t(T) * kD * 2;
-#pragma unroll
-    for (int i = 0; i < kVLoads; ++i) dma16(vpage, voff[i], v_lds + uint32_t(i * kQW) * 1024u);
+  auto copy_k = [&](const Unit& u, uint32_t buf, int t) {
+    dma16(u.page + (t >> 1) * 128 + uint32_t(8 * (wave + 4 * (t & 1))) * 256u, koff,
+          lds0 + buf * kBuf + uint32_t(wave) * 1024u + uint32_t(t) * 4096u);
   };
+  auto copy_v = [&](const Unit& u, int t) {
+    dma16(u.page + kT * kD * 2 + uint32_t(wave + 4 * t) * 1024u, voff,
+          lds0 + 2 * kBuf + uint32_t(wave) * 1024u + uint32_t(t) * 4096u);
+  };
+  auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
 
-  // Group grp takes list entries grp, grp + kGroups, ...; both groups run
-  // `steps` steps.
-  const int steps = (count + kGroups - 1) / kGroups;
-  int n = grp;
-  bool have = usable(n);
-  if (have) {
-    const uint8_t* p0 = page_of(n);
-    issue_k(p0);
-    issue_v(p0);
-  }
-  for (int step = 0; step < steps; ++step) {
-    const int nn = n + kGroups;
-    const bool have_next = usable(nn);
-    const uint8_t* pnext = have_next ? page_of(nn) : nullptr;
-    const int valid = have ? tile_valid(a.tv, list[n] % a.NT, a.NT, a.tail, T) : 0;
-
-    // K_n has landed once only V_n's loads may still be outstanding.
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(kVLoads));
-    __builtin_amdgcn_s_barrier();
-
-    // S^T = K Q^T : KB blocks of 32 keys x 32 queries.
-    f32x16 s[KB];
-    if (have) {
+  // One tile, its K landed: S, the weights, then (V landed) PV.
+  auto tile = [&](const Unit& cur, const Unit& next, uint32_t nbuf) {
+    bf16x8 x[8], p[2];
+    f32x16 s = f32x16{};
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) s[kb] = f32x16{};
-      __builtin_amdgcn_s_setprio(1);
+    for (int t = 0; t < 4; ++t) copy_v(cur, t);
 #pragma unroll
-      for (int ks = 0; ks < kD / 16; ++ks) {
+    for (int ks = 0; ks < kAhead; ++ks) x[ks] = lds_operand(rk[ks & 3] + uint32_t((ks >> 2) * 8192));
+    fence();
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-          const int r = kb * 32 + ln;
-          const int cc = 2 * ks + g;
-          const bf16x8 kf = as_bf16x8(kbuf[r * kKC + (cc ^ (r & 15))]);
-          s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s[kb], 0, 0, 0);
-        }
-      }
-      schedule_reads_ahead<KB * kD / 16>();
-      __builtin_amdgcn_s_setprio(0);
+    for (int ks = 0; ks < 8; ++ks) {
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[ks], qf[ks], s, 0, 0, 0);
+      if (ks + kAhead < 8) x[ks + kAhead] = lds_operand(rk[(ks + kAhead) & 3] + uint32_t(((ks + kAhead) >> 2) * 8192));
+      if (ks & 1) copy_k(next, nbuf, ks >> 1);
+      fence();
     }
-    // every wave has its K operands in registers: the K buffers can be refilled
-    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-    __builtin_amdgcn_s_barrier();
-    if (have_next) issue_k(pnext);
-
-    bf16x8 pf[KB][2];
-    if (have) {
-      // Padding keys of a chunk's last tile never count.
-      if (valid < T) {
+    if (cur.valid < kT) {                          // padding keys of the tile never count
+      int h4 = 4 * hl;
+      asm volatile("" : "+v"(h4));
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
+      for (int e = 0; e < 16; ++e)
+        if (kw * 32 + 8 * (e >> 2) + h4 + (e & 3) >= cur.valid) s[e] = -INFINITY;
+    }
+    auto weights = [&] {
+      const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+      float rs = 0.f;
 #pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int key = kb * 32 + 8 * (e >> 2) + 4 * g + (e & 3);
-            if (key >= valid) s[kb][e] = -INFINITY;
-          }
+      for (int e = 0; e < 16; e += 2) {
+        const float w0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], c2, -moff));
+        const float w1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e + 1], c2, -moff));
+        const bf16x2 w = {(__bf16)w0, (__bf16)w1};
+        p[e >> 3][e & 7] = w[0];
+        p[e >> 3][(e & 7) + 1] = w[1];
+        rs = __builtin_amdgcn_fdot2_f32_bf16(w, ones, rs, false);
       }
-
+      // the packed weights are formed here: the rescale that may follow rewrites
+      // them, and the fp32 values would otherwise be kept for it
+      asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(rs));
+      return rs;
+    };
+    float rs = weights();
+    // wave-uniform: some lane has no offset yet, or its weights grew too large
+    if (__ballot(!(m > -INFINITY) || rs > kSumBound) != 0) {
       float mx = -INFINITY;
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
+      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[e]);
+      mx = pair_max(mx * c2);                      // c2 > 0
+      const bool had = m > -INFINITY;
+      const float sh = had ? fmaxf(mx - m, 0.f) : 0.f;
+      const float alpha = __builtin_amdgcn_exp2f(-sh);
+      m = had ? m + sh : mx;
+      l *= alpha;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[kb][e]);
-      mx = pair_max(mx);
-      if (__ballot(mx > m + lazy_raw) != 0) {
-        const float mnew = fmaxf(m, mx);
-        const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m - mnew) * c2);
-        m = mnew;
-        l *= alpha;
+      for (int mb = 0; mb < 4; ++mb) o[mb] *= alpha;
+      moff = (m > -INFINITY) ? m : 0.f;
+      rs = weights();
+    }
+    l += rs;
+    meet<4>();                                     // V has landed; K of the next tile may be in flight
+    auto operand = [&](int i) { return lds_operand(rv[i >> 2] + uint32_t(4096 * (i & 3))); };
 #pragma unroll
-        for (int mb = 0; mb < kD / 32; ++mb) o[mb] *= alpha;
-      }
-      const float mb2 = m * c2;
+    for (int i = 0; i < kAhead; ++i) x[i] = operand(i);
+    fence();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[i], p[i >> 2], o[i & 3], 0, 0, 0);
+      if (i + kAhead < 8) x[i + kAhead] = operand(i + kAhead);
+      fence();
+    }
+  };
 
-      // P^T as the B operand: 16-key halves of each 32-key block.
-      float rs = 0.f;
-      const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+  for (int base = 0; base == 0 || base < count; base += kList) {
+    // the tiles of the next kList entries; entries naming a tile outside the
+    // window (stale lists) count no key
+    if (base > 0) meet<0>();                       // the table is no longer read
+    if (wave == 0) {
+      int cnt = 0;
+      const int end = min(count, base + kList), cap = a.nk_cap - first;
+      for (int e0 = base; e0 == 0 || e0 < end; e0 += 256) {
+        uint32_t jj[4];
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          bf16x2 pr[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][8 * hh + 2 * e], c2, -mb2));
-            const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][8 * hh + 2 * e + 1], c2, -mb2));
-            pr[e] = bf16x2{(__bf16)p0, (__bf16)p1};
-            rs = __builtin_amdgcn_fdot2_f32_bf16(pr[e], ones, rs, false);
-          }
-          pf[kb][hh] = __builtin_shufflevector(__builtin_shufflevector(pr[0], pr[1], 0, 1, 2, 3),
-                                               __builtin_shufflevector(pr[2], pr[3], 0, 1, 2, 3),
-                                               0, 1, 2, 3, 4, 5, 6, 7);
+        for (int k = 0; k < 4; ++k) {              // (within the row, so that the count is not waited for)
+          const int e = e0 + 64 * k + lane;
+          jj[k] = e < cap ? uint32_t(list[e]) : 0xffffffffu;
         }
-      l += pair_sum(rs);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t j = e0 + 64 * k + lane < end ? jj[k] : 0xffffffffu;
+          const bool on = j < uint32_t(a.nk) && tile_valid(a.tv, int(j % uint32_t(a.NT)), a.NT, a.tail, kT) > 0;
+          const uint64_t bal = __ballot(on);
+          if (on) sunit[cnt + __popcll(bal & ((uint64_t(1) << lane) - 1))] = j;
+          cnt += __popcll(bal);
+        }
+      }
+      if (lane == 0) sunit[kList] = uint32_t(cnt);
     }
-
-    // V_n has landed once only K_{n+kGroups}'s loads may still be outstanding.
-    if (have_next)
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm(kKLoads));
-    else
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-    __builtin_amdgcn_s_barrier();
-
-    // O^T += V^T P^T : 4 blocks of 32 dims x 32 queries.
-    if (have) {
-      __builtin_amdgcn_s_setprio(1);
+    meet<0>();
+    const int U = __builtin_amdgcn_readfirstlane(sunit[kList]);
+    if (U == 0) continue;
+    auto entry = [&](int u) { return uint32_t(__builtin_amdgcn_readfirstlane(sunit[min(u, U - 1)])); };
+    Unit cur = unit(entry(0)), next = unit(entry(1));
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
+    for (int t = 0; t < 4; ++t) copy_k(cur, 0, t);
+    for (int u = 0; u < U; ++u) {
+      meet<0>();                                   // K of tile u has landed; its next buffer and V's are free
+      const uint32_t x2 = sunit[min(u + 2, U - 1)];
+      tile(cur, next, uint32_t(u + 1) & 1u);       // past the end the last K is copied again, and not read
+      const uint32_t d = (u & 1) ? uint32_t(-int(kBuf)) : kBuf;
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-          for (int mb = 0; mb < kD / 32; ++mb) {
-            const int d = mb * 32 + ln;
-            const int cc = 2 * (2 * kb + hh) + g;
-            const bf16x8 vf = as_bf16x8(vbuf[d * kVC + (cc ^ (d & (kVC - 1)))]);
-            o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[kb][hh], o[mb], 0, 0, 0);
-          }
-      schedule_reads_ahead<KB * 2 * kD / 32>();
-      __builtin_amdgcn_s_setprio(0);
+      for (int j = 0; j < 4; ++j) rk[j] += d;
+      cur = next;
+      next = unit(__builtin_amdgcn_readfirstlane(x2));
     }
-    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-    __builtin_amdgcn_s_barrier();
-    if (have_next) issue_v(pnext);
-    n = nn;
-    have = have_next;
+    if (U & 1) {                                   // the next entries start in buffer 0 again
+#pragma unroll
+      for (int j = 0; j < 4; ++j) rk[j] -= kBuf;
+    }
   }
 
-  // ---- merge the two key groups: group 1 hands (m, l, O) to group 0 ----
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-  __syncthreads();   // every copy and operand read of the loop is done
-  float* xo = reinterpret_cast<float*>(&sK[0][0]);   // [kQW][4][16][64 lanes]
-  if (grp != 0) {
-    sML[qw][0][lane] = m;
-    sML[qw][1][lane] = l;
+  // ---- merge the two key blocks: block 1 hands (m, l, O) to block 0 ----
+  l = pair_sum(l);
+  meet<0>();                                       // every copy and operand read is done
+  float* xo = reinterpret_cast<float*>(&sbuf[0][0]);   // [2 query blocks][4][16][64 lanes], then m and l
+  float* xm = xo + 2 * 4 * 16 * 64;
+  if (kw != 0) {
+    xm[qw * 128 + lane] = m;
+    xm[qw * 128 + 64 + lane] = l;
 #pragma unroll
-    for (int mb = 0; mb < kD / 32; ++mb)
+    for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
       for (int e = 0; e < 16; ++e) xo[((qw * 4 + mb) * 16 + e) * 64 + lane] = o[mb][e];
   }
-  __syncthreads();
-  if (grp != 0) return;
-  const float m1 = sML[qw][0][lane], l1 = sML[qw][1][lane];
+  meet<0>();
+  if (kw != 0) return;
+  const float m1 = xm[qw * 128 + lane], l1 = xm[qw * 128 + 64 + lane];
   const float mm = fmaxf(m, m1);
-  const float f0 = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m - mm) * c2);
-  const float f1 = (m1 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m1 - mm) * c2);
+  const float f0 = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - mm);
+  const float f1 = (m1 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m1 - mm);
   const float lt = l * f0 + l1 * f1;
   auto merged = [&](int mb, int e) { return o[mb][e] * f0 + xo[((qw * 4 + mb) * 16 + e) * 64 + lane] * f1; };
 
   if (SPLIT && partial) {
-    // partial: O relative to the offset mm*c2 (base 2) and the row sum
+    // partial: O relative to the offset mm and the row sum
     if (qvalid) {
       const size_t wrow = size_t(row - a.split_from) * a.split + part;
-      float* op = a.work + (wrow * T + qw * 32 + ln) * kD;
+      float* op = a.work + (wrow * kT + qw * 32 + ln) * kD;
 #pragma unroll
-      for (int mb = 0; mb < kD / 32; ++mb)
+      for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int d0 = mb * 32 + 8 * i + 4 * g;
+          const int d0 = mb * 32 + 8 * i + 4 * hl;
           *reinterpret_cast<float4*>(op + d0) = make_float4(merged(mb, 4 * i), merged(mb, 4 * i + 1),
                                                             merged(mb, 4 * i + 2), merged(mb, 4 * i + 3));
         }
-      if (g == 0) {
+      if (hl == 0) {
         const size_t wrows = (size_t(a.B) * a.H * a.NT - a.split_from) * a.split;
-        float2* ml = reinterpret_cast<float2*>(a.work + wrows * T * kD);
-        ml[wrow * T + qw * 32 + ln] = make_float2(mm == -INFINITY ? -INFINITY : mm * c2, lt);
+        float2* ml = reinterpret_cast<float2*>(a.work + wrows * kT * kD);
+        ml[wrow * kT + qw * 32 + ln] = make_float2(mm, lt);
       }
     }
     return;
@@ -340,17 +315,17 @@ __global__ __launch_bounds__(T * 4, 1) void attn_fwd_kernel(AttnArgs a) {
     const float inv = (lt > 0.f) ? 1.f / lt : 0.f;
     uint16_t* op = a.o + ((size_t(b) * a.L + qrow) * a.H + h) * kD;
 #pragma unroll
-    for (int mb = 0; mb < kD / 32; ++mb)
+    for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int d0 = mb * 32 + 8 * i + 4 * g;
+        const int d0 = mb * 32 + 8 * i + 4 * hl;
         uint2 u;
         u.x = pack_bf16x2(merged(mb, 4 * i + 0) * inv, merged(mb, 4 * i + 1) * inv);
         u.y = pack_bf16x2(merged(mb, 4 * i + 2) * inv, merged(mb, 4 * i + 3) * inv);
         *reinterpret_cast<uint2*>(op + d0) = u;
       }
-    if (a.lse != nullptr && g == 0)
-      a.lse[(size_t(b) * a.H + h) * a.L + qrow] = (lt > 0.f) ? mm * a.scale + logf(lt) : -INFINITY;
+    if (a.lse != nullptr && hl == 0)
+      a.lse[(size_t(b) * a.H + h) * a.L + qrow] = (lt > 0.f) ? (mm + log2f(lt)) * 0.69314718055994531f : -INFINITY;
   }
 }
 
@@ -358,14 +333,14 @@ __global__ __launch_bounds__(T * 4, 1) void attn_fwd_kernel(AttnArgs a) {
 
 hipError_t launch_attn_fwd_t64(const AttnArgs& a, hipStream_t stream) {
   const unsigned blocks = unsigned(a.B) * unsigned(a.H) * unsigned(a.NT);
-  attn_fwd_kernel<64, false><<<blocks, 256, 0, stream>>>(a);
+  attn_fwd_kernel<false><<<blocks, 256, 0, stream>>>(a);
   return hipGetLastError();
 }
 
 hipError_t launch_attn_fwd_t64_split(const AttnArgs& a, hipStream_t stream) {
   const unsigned rows = unsigned(a.B) * unsigned(a.H) * unsigned(a.NT);
   const unsigned blocks = unsigned(a.split_from) + (rows - unsigned(a.split_from)) * unsigned(a.split);
-  attn_fwd_kernel<64, true><<<blocks, 256, 0, stream>>>(a);
+  attn_fwd_kernel<true><<<blocks, 256, 0, stream>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_attn_split_merge(a, stream);

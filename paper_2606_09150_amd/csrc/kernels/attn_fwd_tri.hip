@@ -72,13 +72,6 @@ constexpr int kBuffers = 9;
 constexpr float kSumBound = 4096.0f;   // lane row-sum bound of one half unit's 16 weights
 constexpr int kUnitCap = 4095;         // non-empty units of a row listed in LDS
 
-// 3-bit XOR pattern of LDS row r (r % 16): bijective in bits 0..2 for either
-// value of bit 3, and in bits 1..3 for either value of bit 0.
-__device__ __forceinline__ int swz(int r) {
-  const int b3 = (r >> 3) & 1;
-  return ((((r >> 2) & 1) ^ b3) << 2) | (r & 2) | ((r & 1) ^ b3);
-}
-
 struct TriState {
   f32x16 o[4];     // O^T [4 x 32 dims][32 queries]
   f32x16 s[2];     // raw S^T of the unit's 64 keys (two blocks of 32)
@@ -87,17 +80,6 @@ struct TriState {
   float moff;      // m, or 0 while m is -inf
   float l;         // this lane's share of the row sum; the partner lane holds the rest
 };
-
-// s_waitcnt vmcnt(n) lgkmcnt(0), then the workgroup barrier.  The signal
-// fences keep the compiler from moving LDS accesses across the barrier.
-template <int N>
-__device__ __forceinline__ void sync_vm() {
-  constexpr int imm = (N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14);
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_s_waitcnt(imm);
-  __builtin_amdgcn_s_barrier();
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
 
 // MFMA phase: O^T += V^T P^T of the previous unit (V^T in the group's buffer
 // VB, 0 or 1) and S^T = K Q^T of the current unit (K in the group's buffer 2).
@@ -464,18 +446,18 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_tri_kernel(AttnArgs a) {
         issue(vcopy(cur, 0, 0));
       }
       if (G == 1) issue(kcopy(cur, 1, 5));
-      sync_vm<0>();
+      meet<0>();
       int ph = 0;
       if (G == 1) {   // phase 0, second softmax phase of unit -2: copy V[1]
         issue(vcopy(cur, 1, 3));
-        if (1 < U) sync_vm<4>(); else sync_vm<0>();
+        if (1 < U) meet<4>(); else meet<0>();
         ph = 1;
       }
       if (G == 2) {   // phases 0 and 1, softmax phases of unit -1: copy K[2], V[2]
         issue(kcopy(cur, 2, 8));
-        sync_vm<63>();
+        meet<63>();
         issue(vcopy(cur, 2, 6));
-        if (2 < U) sync_vm<4>(); else sync_vm<0>();
+        if (2 < U) meet<4>(); else meet<0>();
         ph = 2;
       }
       // one cycle of unit u: MFMA, first and second softmax phases.  Q = 0:
@@ -490,7 +472,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_tri_kernel(AttnArgs a) {
         __builtin_amdgcn_s_setprio(2);
         tri_mfma<VPV>(st, qf, rg, lds);
         __builtin_amdgcn_s_setprio(1);
-        sync_vm<63>();
+        meet<63>();
         if (++ph == P) return false;
         // first softmax phase: K of unit u+3 into buffer G
         const Unit nxt = unit(u + 3);
@@ -498,13 +480,13 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_tri_kernel(AttnArgs a) {
         tri_first(st, cur.valid, hl, c2, kc, lane_off);
         pin_first(st);
         __builtin_amdgcn_s_setprio(0);
-        sync_vm<63>();
+        meet<63>();
         if (++ph == P) return false;
         // second softmax phase: V of unit u+3
         const HalfCopy vc = vcopy(nxt, u + 3, VNEW);
         tri_second(st, c2, vc, lane_off);
         pin_second(st);
-        if (vc.on) sync_vm<4>(); else sync_vm<0>();
+        if (vc.on) meet<4>(); else meet<0>();
         cur = nxt;
         return ++ph != P;
       };
@@ -523,7 +505,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_tri_kernel(AttnArgs a) {
 
   // ---- merge the three key groups: groups 1 and 2 hand (m, l, O) to group 0 ----
   st.l = pair_sum(st.l);
-  sync_vm<0>();   // every copy and operand read of the loop is done
+  meet<0>();   // every copy and operand read of the loop is done
   float* xo = reinterpret_cast<float*>(&sbuf[0][0]);                    // [8 waves][4][16][64 lanes]: 128 KB
   float* xm = reinterpret_cast<float*>(&sbuf[0][0]) + 8 * 4 * 16 * 64;  // [2][8 waves][64 lanes]: m, then l
   if (grp != 0) {
@@ -535,7 +517,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_tri_kernel(AttnArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) xo[((w * 4 + mb) * 16 + e) * 64 + lane] = st.o[mb][e];
   }
-  sync_vm<0>();
+  meet<0>();
   if (grp == 0) {
     const int w1 = qw, w2 = 4 + qw;
     const float mB = xm[w1 * 64 + lane], lB = xm[512 + w1 * 64 + lane];

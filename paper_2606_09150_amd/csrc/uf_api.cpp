@@ -474,7 +474,8 @@ int uf_sparse_causal_attn_fwd_split(const uf_kv* kv, const void* d_q, const void
 int uf_attn_tail_plan(const uf_kv* kv, int32_t n_cu, int32_t* split_from, int32_t* n_split) {
   if (kv == nullptr || split_from == nullptr || n_split == nullptr) return fail(UF_ERR_ARG, "null argument");
   if (n_cu < 1) return fail(UF_ERR_ARG, "n_cu must be >= 1");
-  // workgroups resident at once: one per CU with either tile size
+  // rounds of one workgroup per CU (128-token tiles; three 64-token ones fit one
+  // CU, where the plan keeps the same count)
   const int64_t R = kv->layout().rows, C = int64_t(n_cu);
   *split_from = int32_t(R);
   *n_split = 1;

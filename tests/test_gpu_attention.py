@@ -486,6 +486,37 @@ def test_split_kv_parity_t64(n_split):
     assert row_rel_err(case._host(os_), case._host(o1)) <= REL_TOL
 
 
+# 64-token tiles: a wave takes 32 keys of every tile and 32 queries, so last tiles
+# that end around 32 leave the second key block or query block empty.
+@pytest.mark.parametrize("L", [1, 31, 32, 33, 63, 64, 65, 96, 97, 129])
+def test_t64_tile_edges(L):
+    P = require_gpu()
+    log(f"attn t64 edges L={L}")
+    case = Case(P, 2, L, 2, 64, 3, True, seed=1400 + L)
+    for _ in range(4):
+        case.append()
+    rule = case.rule(0.4)
+    case.gpu_lists(rule)
+    _full_check(case, rule, case.query())
+
+
+# ... and a row's list is taken into LDS 1,024 entries at a time: 1,088 of them,
+# whole and in slices, with an odd number in the second part as well.
+@pytest.mark.parametrize("p,split", [(1.0, None), (0.97, None), (1.0, (3, 5))])
+def test_t64_long_lists(p, split):
+    P = require_gpu()
+    log(f"attn t64 long lists p={p} split={split}")
+    case = Case(P, 1, 1025, 1, 64, 64, True, seed=1450, gen_device="cuda")
+    for _ in range(64):
+        case.append()
+    rule = case.rule(p)
+    case.gpu_lists(rule)
+    q = case.query()
+    o, lse = case.win.attention(q, 1 / math.sqrt(128), split=split)
+    torch.cuda.synchronize()
+    _sampled_check(case, rule, q, [(0, 0, r) for r in (0, 31, 32, 63, 200, 500, 1000, 1024)], o=o, lse=lse)
+
+
 def test_tiny_workload_split_rows():
     """The tiny workload (6 rows of 64-token tiles, too short for the plan to
     split) with every row cut into one slice per key tile, in full against the
