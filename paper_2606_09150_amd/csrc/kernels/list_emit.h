@@ -1,9 +1,11 @@
-// Output stage shared by the list builders: one workgroup of 256 lanes writes
-// the list row of one (b, h, query tile) from a keep predicate over logical
-// key tiles 0 .. nk_cap-1 (false at and beyond nk).  Each pass decides 256
-// consecutive tiles; a wave ballot gives two 32-bit mask words per wave and a
-// prefix over the four wave counts places the kept indices in ascending
-// order; the tail of the row is padded with -1.
+// Output stage shared by the list builders: one wave (emit_row_wave) or one
+// workgroup of 256 lanes (emit_row) writes the list row of one (b, h, query
+// tile) from a keep predicate over logical key tiles 0 .. nk_cap-1 (false at
+// and beyond nk).  A wave ballot gives two 32-bit mask words; the kept indices
+// are placed in ascending order, and the tail of the row is padded with -1.
+// A wave per row needs no barrier (four rows run side by side in a workgroup);
+// a workgroup per row takes 256 tiles per pass with two barriers, and is for the
+// longest rows.
 #pragma once
 
 #include "../launch.h"
@@ -13,6 +15,30 @@ namespace lists {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
+
+template <class Keep>
+__device__ void emit_row_wave(Keep keep_of, int nk_cap, int mask_words, int32_t* count, int32_t* idx, uint32_t* mask) {
+  const int lane = threadIdx.x & 63;
+  int base = 0;
+  for (int j0 = 0; j0 < nk_cap; j0 += 256) {
+    bool keep[4];                            // four words decided side by side
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int j = j0 + 64 * k + lane;
+      keep[k] = (j < nk_cap) && keep_of(j);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint64_t ballot = __ballot(keep[k]);
+      const int w0 = (j0 + 64 * k) >> 5;
+      if (lane < 2 && w0 + lane < mask_words) mask[w0 + lane] = uint32_t(ballot >> (32 * lane));
+      if (keep[k]) idx[base + __popcll(ballot & ((1ull << lane) - 1ull))] = j0 + 64 * k + lane;
+      base += __popcll(ballot);
+    }
+  }
+  for (int j = base + lane; j < nk_cap; j += 64) idx[j] = -1;
+  if (lane == 0) *count = base;
+}
 
 // `wave_count` is a __shared__ int[kWaves] of the calling kernel.  Every lane
 // of the workgroup must call this (it contains barriers).

@@ -7,8 +7,8 @@
 // key tile kept iff the upper 32 bits of a SplitMix64 chain over
 // (b, h, seq(current), i, seq(chunk), t) fall below floor(p * 2^32).
 //
-// One workgroup of 256 lanes per list row; the row is written by the shared
-// output stage (list_emit.h).  Integer-only, so the lists are bit-exact.
+// One wave per list row, four rows per workgroup; the row is written by the
+// shared output stage (list_emit.h).  Integer-only, so the lists are bit-exact.
 #include "list_emit.h"
 
 namespace uf {
@@ -27,9 +27,19 @@ __device__ inline uint64_t splitmix64(uint64_t z) {
 }
 
 __global__ __launch_bounds__(kThreads) void tile_lists_kernel(ListArgs a) {
-  __shared__ int wave_count[kWaves];
-
-  const int row = blockIdx.x;
+  // the chunks' sequence numbers, and whether the rule keeps them whole, in LDS:
+  // indexed by a lane's tile, kernel arguments are vector loads from memory
+  // that is not cached, one round trip per 256 tiles
+  __shared__ uint64_t sseq[UF_MAX_CHUNKS];
+  __shared__ int sforced[UF_MAX_CHUNKS];
+  if (threadIdx.x < UF_MAX_CHUNKS) {
+    const int p = threadIdx.x;
+    sseq[p] = uint64_t(a.seq[p]);
+    sforced[p] = (a.sink[p] && a.keep_sink) || (a.seq[p] == a.cur_seq && a.keep_current);
+  }
+  __syncthreads();
+  const int row = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (row >= a.rows) return;
   const int i = row % a.NT;
   const int bh = row / a.NT;
   const int h = bh % a.H;
@@ -49,18 +59,18 @@ __global__ __launch_bounds__(kThreads) void tile_lists_kernel(ListArgs a) {
     const int pos = j / a.NT;
     const int t = j - pos * a.NT;
     if (!tile_local(a.tv, i, t)) return false;   // structural local window (block geometry)
-    if ((a.sink[pos] && a.keep_sink) || (a.seq[pos] == a.cur_seq && a.keep_current)) return true;
-    uint64_t y = splitmix64(x ^ uint64_t(a.seq[pos]));
+    if (sforced[pos]) return true;
+    uint64_t y = splitmix64(x ^ sseq[pos]);
     y = splitmix64(y ^ uint64_t(t));
     return (y >> 32) < a.thr;
   };
-  lists::emit_row(keep_of, a.nk_cap, a.mask_words, counts + row, idx, mask, wave_count);
+  lists::emit_row_wave(keep_of, a.nk_cap, a.mask_words, counts + row, idx, mask);
 }
 
 }  // namespace
 
 hipError_t launch_tile_lists(const ListArgs& a, hipStream_t stream) {
-  tile_lists_kernel<<<unsigned(a.rows), kThreads, 0, stream>>>(a);
+  tile_lists_kernel<<<unsigned(a.rows + kWaves - 1) / kWaves, kThreads, 0, stream>>>(a);
   return hipGetLastError();
 }
 

@@ -16,17 +16,25 @@
 // multiply-add disabled; scores compare through the unsigned key that orders
 // float32 like the real line, equal keys going to the lower tile index.
 //
-// Two kernels.  pool_queries: one workgroup per query tile stages the tile's
+// Three kernels.  pool_queries: one workgroup per query tile stages the tile's
 // valid rows in LDS and lane d adds column d in token order, writing the
-// pooled query into the list buffer's scratch section.  topk_lists: one
-// workgroup of 256 lanes per (b, h, group of G query tiles); a lane takes one
-// ranked candidate at a time, loads its pooled key (512 bytes, L2-resident)
-// into registers and scores it against the G pooled queries held in LDS.  The
-// selection of a row runs in one wave: a radix select over the order keys
-// (four passes of 8-bit histograms in LDS) finds the budget-th largest key,
-// then one ballot pass over the candidates in index order keeps every larger
-// key and the first equal keys the budget still admits (ties to the lower
-// index).  Each row is then written by the shared output stage.
+// pooled query into the list buffer's scratch section.  topk_scores: one
+// workgroup per head, 32 query tiles and 32 ranked candidates, both sides'
+// pooled vectors in LDS, two by two scores per lane (four independent chains);
+// the order keys go to the row's index section, which is at least as long and is
+// rewritten last.  topk_select: one wave per row (four waves for the longest
+// rows) holds the row's keys in registers and finds the budget-th largest one
+// bit by bit, from ballots: the largest T with at least `budget` keys >= T, ending
+// as soon as the count is exact.  Every larger key is kept, then the first equal
+// ones (ties to the lower index), and the wave writes its row.
+//
+// What bounds them: pool_queries reads Q (75 MB at 1K, 18 us); the scores are
+// 2 x 128 unfused operations per pair (about 9 us of vector issue at 1K, 2,304
+// rows by 576 candidates); the selection is latency.  One kernel that scored two
+// query tiles against every candidate read each pooled key once per two rows (340
+// MB from L2) and selected with histograms in two of its four waves: 66 us for
+// what topk_scores and topk_select now do in 15 + 13 us.  Windows with few
+// rows and candidates take two kernels: topk_select computes its row's keys.
 #include "list_emit.h"
 
 #pragma clang fp contract(off)
@@ -37,7 +45,6 @@ namespace {
 using lists::kThreads;
 using lists::kWaves;
 constexpr int kD = 128;
-constexpr int kMaxG = 8;
 
 __device__ inline float bf16_to_f32(uint16_t x) { return __uint_as_float(uint32_t(x) << 16); }
 
@@ -73,164 +80,253 @@ __global__ __launch_bounds__(kThreads) void pool_queries_kernel(TopkArgs a) {
   }
 }
 
-__global__ __launch_bounds__(kThreads) void topk_lists_kernel(TopkArgs a) {
-  extern __shared__ uint32_t dyn[];
-  __shared__ float qm[kMaxG][kD];
-  __shared__ uint32_t whist[kWaves][256];
-  __shared__ int wave_count[kWaves];
+constexpr int kTile = 32;                 // query tiles and candidates of a workgroup
+constexpr int kRow = kD + 4;              // LDS row in floats: 16 rows' chunks cover all banks
 
-  const int nc = max(a.cand_hi - a.cand_lo, 0);   // ranked candidates of a row
-  uint32_t* keys = dyn;                            // [G][nc]
-  uint8_t* sel = reinterpret_cast<uint8_t*>(dyn + size_t(a.G) * nc);   // [G][nc]
-
-  const int groups = (a.NT + a.G - 1) / a.G;
-  const int grp = blockIdx.x % groups;
-  const int bh = blockIdx.x / groups;
-  const int i0 = grp * a.G;
-  const int gn = min(a.G, a.NT - i0);
-  const int tid = threadIdx.x;
-
-  // 1. pooled queries of the group
-  const float* qmean = reinterpret_cast<const float*>(a.lists + a.scratch_offset);
-  for (int e = tid; e < gn * kD; e += kThreads) qm[e / kD][e % kD] = qmean[(size_t(bh) * a.NT + i0) * kD + e];
-  __syncthreads();
-
-  // 2. scores: lane takes candidate m, its pooled key in registers
+__global__ __launch_bounds__(kThreads) void topk_scores_kernel(TopkArgs a) {
+  __shared__ float4 sq[kTile * kRow / 4], sk[kTile * kRow / 4];
+  const int nc = a.cand_hi - a.cand_lo;    // ranked candidates of a row
+  const unsigned mt = unsigned(nc + kTile - 1) / kTile, it = unsigned(a.NT + kTile - 1) / kTile;
+  const int m0 = int(blockIdx.x % mt) * kTile, i0 = int(blockIdx.x / mt % it) * kTile, bh = int(blockIdx.x / mt / it);
+  const float4* qmean = reinterpret_cast<const float4*>(a.lists + a.scratch_offset);
   const size_t slot_pages = size_t(a.B) * a.H * a.NT;
-  const size_t head_page = size_t(bh) * a.NT;
-  for (int m = tid; m < nc; m += kThreads) {
-    const int j = a.cand_lo + m;
+  // 32 rows of 32 chunks each, two rows per wave and pass (so that a row's slot is
+  // a scalar load of the kernel arguments); rows past the end repeat the last
+  // one, and are not written
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool odd = (threadIdx.x & 32) != 0;
+  const int cc = threadIdx.x & 31;
+  auto pooled = [&](int r) {
+    const int j = a.cand_lo + min(m0 + r, nc - 1);
     const int pos = j / a.NT;
-    const int t = j - pos * a.NT;
-    const float4* kp = reinterpret_cast<const float4*>(a.kmean + (size_t(a.slot_of[pos]) * slot_pages + head_page + t) * kD);
-    float4 k4[kD / 4];
+    return reinterpret_cast<const float4*>(a.kmean) +
+           (size_t(a.slot_of[pos]) * slot_pages + size_t(bh) * a.NT + (j - pos * a.NT)) * (kD / 4);
+  };
 #pragma unroll
-    for (int c = 0; c < kD / 4; ++c) k4[c] = kp[c];
-    for (int g = 0; g < gn; ++g) {
-      float acc = 0.f;
+  for (int k = 0; k < kTile / 8; ++k) {
+    const int ra = 8 * k + 2 * wave, r = odd ? ra + 1 : ra;
+    const float4* pa = pooled(ra);
+    const float4* pb = pooled(ra + 1);
+    sq[r * (kRow / 4) + cc] = qmean[(size_t(bh) * a.NT + min(i0 + r, a.NT - 1)) * (kD / 4) + cc];
+    sk[r * (kRow / 4) + cc] = (odd ? pb : pa)[cc];
+  }
+  __syncthreads();
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;   // candidates tx, tx + 16; rows ty, ty + 16
+  float acc[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
+#pragma unroll 8
+  for (int c = 0; c < kD / 4; ++c) {
+    float4 q[2], k[2];
 #pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      q[u] = sq[(ty + 16 * u) * (kRow / 4) + c];
+      k[u] = sk[(tx + 16 * u) * (kRow / 4) + c];
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        acc[u][v] = acc[u][v] + q[u].x * k[v].x;
+        acc[u][v] = acc[u][v] + q[u].y * k[v].y;
+        acc[u][v] = acc[u][v] + q[u].z * k[v].z;
+        acc[u][v] = acc[u][v] + q[u].w * k[v].w;
+      }
+  }
+  uint32_t* keys = reinterpret_cast<uint32_t*>(a.lists + a.idx_offset);
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      const int i = i0 + ty + 16 * u, m = m0 + tx + 16 * v;
+      if (i < a.NT && m < nc) keys[(size_t(bh) * a.NT + i) * a.nk_cap + m] = order_key(acc[u][v]);
+    }
+}
+
+// W waves per row, K keys per lane (64 W K >= candidates).  RANK: the budget
+// cuts the candidates (otherwise all of them are kept, or none).  SCORE: the
+// row's wave computes its keys itself (a lane takes a candidate) instead of
+// reading those of topk_scores.
+template <int W, int K, bool RANK, bool SCORE>
+__global__ __launch_bounds__(kThreads) void topk_select_kernel(TopkArgs a) {
+  constexpr int kRows = kWaves / W;        // rows of a workgroup
+  constexpr int kWords = W * K;            // 64-candidate words of a row
+  __shared__ uint64_t sgt[RANK ? kRows : 1][RANK ? kWords : 1], seq[RANK ? kRows : 1][RANK ? kWords : 1];
+  __shared__ int part[2][kWaves];
+  const int nc = max(a.cand_hi - a.cand_lo, 0);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int sub = wave % W, slot = wave / W;
+  const int row = blockIdx.x * kRows + slot;
+  if (row >= a.B * a.H * a.NT) return;     // W = 1 only: whole waves, and no barrier follows
+  int32_t* idx = reinterpret_cast<int32_t*>(a.lists + a.idx_offset) + size_t(row) * a.nk_cap;
+
+  if constexpr (RANK) {
+    // candidate 64 (sub + W i) + lane; a key of 0 past the end is below every trial value
+    uint32_t key[K];
+    if constexpr (SCORE) {
+      __shared__ float4 sqm[kRows][kD / 4];
+      const int bh = row / a.NT;
+      if (lane < kD / 4)
+        sqm[slot][lane] = reinterpret_cast<const float4*>(a.lists + a.scratch_offset)[size_t(row) * (kD / 4) + lane];
+      __builtin_amdgcn_wave_barrier();
+      const float4* kp[K];
+      float acc[K];
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        const int j = a.cand_lo + min(64 * i + lane, nc - 1);
+        const int pos = j / a.NT;
+        kp[i] = reinterpret_cast<const float4*>(a.kmean) +
+                (size_t(a.slot_of[pos]) * a.B * a.H * a.NT + size_t(bh) * a.NT + (j - pos * a.NT)) * (kD / 4);
+        acc[i] = 0.f;
+      }
+#pragma unroll 8
       for (int c = 0; c < kD / 4; ++c) {
-        acc = acc + qm[g][4 * c + 0] * k4[c].x;
-        acc = acc + qm[g][4 * c + 1] * k4[c].y;
-        acc = acc + qm[g][4 * c + 2] * k4[c].z;
-        acc = acc + qm[g][4 * c + 3] * k4[c].w;
-      }
-      keys[size_t(g) * nc + m] = order_key(acc);
-    }
-  }
-  __syncthreads();
-
-  // 3. selection, one wave per row
-  {
-    const int wave = tid >> 6;
-    const int lane = tid & 63;
-    uint32_t* hist = whist[wave];
-    for (int g = wave; g < gn; g += kWaves) {
-      const uint32_t* row = keys + size_t(g) * nc;
-      uint8_t* sg = sel + size_t(g) * nc;
-      if (a.budget >= nc || a.budget == 0) {
-        for (int m = lane; m < nc; m += 64) sg[m] = a.budget > 0 ? 1 : 0;
-        continue;
-      }
-      // radix select: `need` = rank of the wanted key among keys matching `prefix` on `pmask`
-      uint32_t prefix = 0, pmask = 0;
-      int need = a.budget;
-      for (int shift = 24; shift >= 0; shift -= 8) {
-        for (int e = lane; e < 256; e += 64) hist[e] = 0;
-        __builtin_amdgcn_wave_barrier();
-        for (int m = lane; m < nc; m += 64) {
-          const uint32_t k = row[m];
-          if ((k & pmask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1u);
-        }
-        __builtin_amdgcn_wave_barrier();
-        // lane l holds bins 255-4l .. 252-4l (descending); exclusive prefix over lanes
-        uint32_t hb[4];
-        uint32_t own = 0;
+        const float4 q = sqm[slot][c];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          hb[e] = hist[255 - 4 * lane - e];
-          own += hb[e];
+        for (int i = 0; i < K; ++i) {
+          const float4 k = kp[i][c];
+          acc[i] = acc[i] + q.x * k.x;
+          acc[i] = acc[i] + q.y * k.y;
+          acc[i] = acc[i] + q.z * k.z;
+          acc[i] = acc[i] + q.w * k.w;
         }
-        uint32_t incl = own;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const uint32_t y = __shfl_up(incl, o);
-          if (lane >= o) incl += y;
-        }
-        const uint32_t excl = incl - own;
-        // the lane whose bins cover rank `need`
-        const bool mine = excl < uint32_t(need) && uint32_t(need) <= incl;
-        const int owner = __ffsll(static_cast<long long>(__ballot(mine))) - 1;
-        int bin = 0;
-        uint32_t above = excl;
-        if (mine) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (above + hb[e] >= uint32_t(need)) {
-              bin = 255 - 4 * lane - e;
-              break;
-            }
-            above += hb[e];
-          }
-        }
-        bin = __shfl(bin, owner);
-        above = __shfl(above, owner);
-        prefix |= uint32_t(bin) << shift;
-        pmask |= 255u << shift;
-        need -= int(above);
-        __builtin_amdgcn_wave_barrier();
       }
-      // keys above the threshold, and the first `need` keys equal to it in index order
-      int taken = 0;
-      for (int m0 = 0; m0 < nc; m0 += 64) {
-        const int m = m0 + lane;
-        const uint32_t k = (m < nc) ? row[m] : 0u;
-        const bool eq = (m < nc) && k == prefix;
-        const uint64_t eqb = __ballot(eq);
-        const int rank = taken + __popcll(eqb & ((1ull << lane) - 1ull));
-        if (m < nc) sg[m] = (k > prefix || (eq && rank < need)) ? 1 : 0;
-        taken += __popcll(eqb);
+#pragma unroll
+      for (int i = 0; i < K; ++i) key[i] = 64 * i + lane < nc ? order_key(acc[i]) : 0u;
+    } else {
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        const int m = 64 * (sub + W * i) + lane;
+        key[i] = m < nc ? uint32_t(idx[m]) : 0u;
       }
     }
-  }
-  __syncthreads();
-
-  // 4. the list rows
-  int32_t* counts = reinterpret_cast<int32_t*>(a.lists);
-  for (int g = 0; g < gn; ++g) {
-    const int row = bh * a.NT + i0 + g;
-    int32_t* idx = reinterpret_cast<int32_t*>(a.lists + a.idx_offset) + size_t(row) * a.nk_cap;
-    uint32_t* mask = reinterpret_cast<uint32_t*>(a.lists + a.mask_offset) + size_t(row) * a.mask_words;
-    const uint8_t* sg = sel + size_t(g) * nc;
-    const int qi = i0 + g;
-    auto keep_of = [&](int j) {
-      if (j >= a.nk) return false;
-      if (!tile_local(a.tv, qi, j % a.NT)) return false;   // structural local window (block geometry)
-      if (j < a.cand_lo || j >= a.cand_hi) return true;    // forced: pinned or current chunk
-      return sg[j - a.cand_lo] != 0;
+    int flip = 0;
+    auto total = [&](int c) {              // over the row's waves
+      if constexpr (W > 1) {
+        if (lane == 0) part[flip][wave] = c;
+        __syncthreads();
+        c = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) c += part[flip][w];
+        flip ^= 1;
+      }
+      return __builtin_amdgcn_readfirstlane(c);
     };
-    lists::emit_row(keep_of, a.nk_cap, a.mask_words, counts + row, idx, mask, wave_count);
+    uint32_t T = 0;
+    bool exact = false;
+    for (int bit = 31; bit >= 0 && !exact; --bit) {
+      const uint32_t t = T | (1u << bit);
+      int c = 0;
+#pragma unroll
+      for (int i = 0; i < K; ++i) c += __popcll(__ballot(key[i] >= t));
+      c = total(c);
+      if (c >= a.budget) T = t;
+      exact = c == a.budget;
+    }
+    // the keys above T (exact: and T itself, on which the count ended)
+    int above = 0;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      const int m = 64 * (sub + W * i) + lane;
+      const uint64_t gt = __ballot(exact ? key[i] >= T : key[i] > T);
+      const uint64_t eq = __ballot(!exact && m < nc && key[i] == T);
+      above += __popcll(gt);
+      if (lane == 0) {
+        sgt[slot][sub + W * i] = gt;
+        seq[slot][sub + W * i] = eq;
+      }
+    }
+    const int need = a.budget - total(above);   // equal keys still admitted, in index order
+    if constexpr (W > 1) __syncthreads();
+    else __builtin_amdgcn_wave_barrier();
+    if (sub == 0) {
+      constexpr int kPer = (kWords + 63) / 64;
+      int before = 0;
+      uint64_t w[kPer];
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const int n = lane * kPer + u;
+        w[u] = n < kWords ? seq[slot][n] : 0;
+        before += __popcll(w[u]);
+      }
+      const int own = before;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(before, o);
+        if (lane >= o) before += y;
+      }
+      int left = need - (before - own);
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const int n = lane * kPer + u;
+        uint64_t take = 0, rest = w[u];
+        const int equal = int(__popcll(rest));   // (the builtin's type is unsigned)
+        if (left >= equal) take = rest;
+        else
+          for (int e = 0; e < left; ++e) {       // the lowest `left` bits
+            take |= rest & -rest;
+            rest &= rest - 1;
+          }
+        left -= equal;
+        if (n < kWords) sgt[slot][n] |= take;
+      }
+    }
+    if constexpr (W > 1) __syncthreads();
+    else __builtin_amdgcn_wave_barrier();
   }
+
+  const int qi = row % a.NT;
+  auto keep_of = [&](int j) {
+    if (j >= a.nk) return false;
+    if (!tile_local(a.tv, qi, j % a.NT)) return false;   // structural local window (block geometry)
+    if (j < a.cand_lo || j >= a.cand_hi) return true;    // forced: pinned or current chunk
+    if constexpr (!RANK) return a.budget > 0;
+    const int m = j - a.cand_lo;
+    return ((sgt[slot][m >> 6] >> (m & 63)) & 1u) != 0;
+  };
+  int32_t* count = reinterpret_cast<int32_t*>(a.lists) + row;
+  uint32_t* mask = reinterpret_cast<uint32_t*>(a.lists + a.mask_offset) + size_t(row) * a.mask_words;
+  if constexpr (W == 1)
+    lists::emit_row_wave(keep_of, a.nk_cap, a.mask_words, count, idx, mask);
+  else
+    lists::emit_row(keep_of, a.nk_cap, a.mask_words, count, idx, mask, part[0]);
 }
 
 }  // namespace
 
-hipError_t launch_topk_lists(const TopkArgs& a, size_t lds_bytes, hipStream_t stream) {
-  // the candidate keys and flags may take more than the default dynamic LDS
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(topk_lists_kernel),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     kTopkMaxCandidates * 5);
-  if (attr != hipSuccess) return attr;
+hipError_t launch_topk_lists(const TopkArgs& a, hipStream_t stream) {
   const unsigned rows = unsigned(a.B) * unsigned(a.H) * unsigned(a.NT);
+  const int nc = a.cand_hi > a.cand_lo ? a.cand_hi - a.cand_lo : 0;
+  hipError_t e = hipSuccess;
+  // a budget of none or of every candidate needs no score
+  if (a.budget == 0 || a.budget >= nc) {
+    topk_select_kernel<1, 1, false, false><<<(rows + 3) / 4, kThreads, 0, stream>>>(a);
+    return hipGetLastError();
+  }
   if (a.T == 128)
     pool_queries_kernel<128><<<rows, kThreads, 0, stream>>>(a);
   else
     pool_queries_kernel<64><<<rows, kThreads, 0, stream>>>(a);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const unsigned groups = unsigned((a.NT + a.G - 1) / a.G);
-  const unsigned blocks = unsigned(a.B) * unsigned(a.H) * groups;
-  topk_lists_kernel<<<blocks, kThreads, lds_bytes, stream>>>(a);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const unsigned four = (rows + 3) / 4;
+  // Few pairs: a launch costs more than reading each pooled key once per row.
+  // Two launches against three: 20 rows x 20 candidates 11 against 15 us, 720 x
+  // 60 13 against 16.5, 1,024 x 64 16 against 18; 720 x 120 17.7 against 17.3,
+  // 2,560 x 64 33.6 against 30.7.
+  if (nc <= 64 * 2 && uint64_t(rows) * uint64_t(nc) <= 80000) {
+    if (nc <= 64) topk_select_kernel<1, 1, true, true><<<four, kThreads, 0, stream>>>(a);
+    else topk_select_kernel<1, 2, true, true><<<four, kThreads, 0, stream>>>(a);
+    return hipGetLastError();
+  }
+  const unsigned tiles = (unsigned(a.NT + kTile - 1) / kTile) * (unsigned(nc + kTile - 1) / kTile);
+  topk_scores_kernel<<<tiles * unsigned(a.B) * unsigned(a.H), kThreads, 0, stream>>>(a);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  // keys per lane: the fewest that hold a row; past 64 a row takes four waves
+  if (nc <= 64 * 4) topk_select_kernel<1, 4, true, false><<<four, kThreads, 0, stream>>>(a);
+  else if (nc <= 64 * 10) topk_select_kernel<1, 10, true, false><<<four, kThreads, 0, stream>>>(a);
+  else if (nc <= 64 * 16) topk_select_kernel<1, 16, true, false><<<four, kThreads, 0, stream>>>(a);
+  else if (nc <= 64 * 32) topk_select_kernel<1, 32, true, false><<<four, kThreads, 0, stream>>>(a);
+  else if (nc <= 64 * 64) topk_select_kernel<1, 64, true, false><<<four, kThreads, 0, stream>>>(a);
+  else topk_select_kernel<4, 64, true, false><<<rows, kThreads, 0, stream>>>(a);
   return hipGetLastError();
 }
 

@@ -71,21 +71,20 @@ struct ListArgs {
 };
 hipError_t launch_tile_lists(const ListArgs& a, hipStream_t stream);
 
-// Top-k lists: one workgroup per (b, h, group of G query tiles).
+// Top-k lists.
 struct TopkArgs {
   const uint16_t* q;      // [B, L, H, D]
   const float* kmean;     // pooled keys: [slots][B][H][NT][D]
   uint8_t* lists;
   size_t idx_offset, mask_offset, scratch_offset;   // scratch: pooled queries [B][H][NT][D]
   int32_t B, H, L, T, NT, tail, nk, nk_cap, mask_words;
-  int32_t G;              // query tiles per workgroup
   int32_t cand_lo, cand_hi;   // ranked logical tiles [cand_lo, cand_hi)
   int32_t budget;
   int32_t slot_of[UF_MAX_CHUNKS];
   TileValid tv;
 };
-constexpr int kTopkMaxCandidates = 16384;   // G * candidates per workgroup
-hipError_t launch_topk_lists(const TopkArgs& a, size_t lds_bytes, hipStream_t stream);
+constexpr int kTopkMaxCandidates = 16384;   // ranked candidates of a row
+hipError_t launch_topk_lists(const TopkArgs& a, hipStream_t stream);
 
 struct AttnArgs {
   const uint16_t* q;      // [B, L, H, D]

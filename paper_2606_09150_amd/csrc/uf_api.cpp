@@ -362,14 +362,12 @@ int uf_build_topk_lists(const uf_kv* kv, const void* d_q, const uf_topk_rule* ru
   a.nk = nk;
   a.nk_cap = kv->nk_cap;
   a.mask_words = kv->mask_words;
-  a.G = std::max(1, std::min({2, kv->nt, uf::kTopkMaxCandidates / std::max(nc, 1)}));
   a.cand_lo = lo;
   a.cand_hi = hi;
   a.budget = rule->budget;
   a.tv = kv->tile_valid(rule->local_r);
   for (size_t p = 0; p < kv->live.size(); ++p) a.slot_of[p] = kv->live[p].slot;
-  const size_t lds = std::max<size_t>(size_t(a.G) * size_t(nc) * 5, 16);
-  hipError_t e = uf::launch_topk_lists(a, lds, static_cast<hipStream_t>(stream));
+  hipError_t e = uf::launch_topk_lists(a, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(UF_ERR_HIP, "topk_lists launch: %s", hipGetErrorString(e));
   return ok();
 }

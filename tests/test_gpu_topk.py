@@ -90,6 +90,24 @@ def test_topk_lists_bit_exact(B, L, H, T, mc, pin, n, budget, keep_sink, keep_cu
     _topk_compare(case, case.query(), oracle.TopkRule(budget, keep_sink, keep_current))
 
 
+# The selection holds a row's keys in 1 or 2 (few pairs, scored in place), 4, 10,
+# 16, 32 or 64 registers per lane, then in four waves: candidate counts at both
+# sides of each limit.  With the same keys
+# in every chunk each score occurs once per chunk, so the budget cuts through ties.
+@pytest.mark.parametrize("chunks,nt", [(2, 32), (5, 13), (2, 64), (3, 43), (4, 64), (1, 257), (10, 64), (1, 641), (16, 64), (25, 41), (32, 64), (3, 683),
+                                       (64, 64), (17, 241)])
+def test_topk_selection_sizes(chunks, nt):
+    P = require_gpu()
+    log(f"topk selection candidates={chunks * nt}")
+    case = Case(P, 1, nt * 64 - 3, 1, 64, chunks, True, seed=4100 + nt, gen_device="cuda")
+    for _ in range(chunks):
+        case.append()
+        case.n_appended = 0
+    q = case._draw(1, "q")
+    for budget in (1, chunks * nt // 3 + 1, chunks * nt - 1):
+        _topk_compare(case, q, oracle.TopkRule(budget, False, False))
+
+
 @pytest.mark.parametrize("name,frac", [("1k", 0.25), ("2k", 0.15)])
 def test_topk_lists_workloads(name, frac):
     """Full-size windows in the bench's configuration, every head, bit for bit."""
