@@ -574,59 +574,70 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_tri_kernel(AttnArgs a) {
   }
 }
 
-// Split-KV merge (tiles of TT tokens): one workgroup per split row; lane (query, half) combines the
-// row's partials for 64 dims: O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
+// Split-KV merge (tiles of TT tokens): 32 lanes per query, each with four
+// dims: O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.  Lane n of the 32 takes the
+// (m, l) of slices n and n + 32; the weights are passed around by lane reads.
+// Latency-bound: a workgroup per 8 queries fills the chip and every partial is
+// requested before any is used (52 rows of 4 slices 5 us; one workgroup per row
+// with 64 dims per lane, which read its slices one after the other, 16.6).
+constexpr int kMergeQueries = 8;
 template <int TT>
-__global__ __launch_bounds__(2 * TT) void attn_split_merge_kernel(AttnArgs a) {
-  const int row = a.split_from + int(blockIdx.x);
+__global__ __launch_bounds__(32 * kMergeQueries) void attn_split_merge_kernel(AttnArgs a) {
+  constexpr int kParts = TT / kMergeQueries;    // workgroups of a row
+  const int k = int(blockIdx.x) / kParts;       // split row
+  const int row = a.split_from + k;
   const int qt = row % a.NT;
   const int bh = row / a.NT;
   const int h = bh % a.H;
   const int b = bh / a.H;
-  const int ql = threadIdx.x >> 1;
-  const int half = threadIdx.x & 1;
+  const int ql = (int(blockIdx.x) % kParts) * kMergeQueries + int(threadIdx.x >> 5);
+  const int ln = threadIdx.x & 31;
   const int qrow = qt * TT + ql;
-  if (qrow >= a.L) return;
+  if (qrow >= a.L) return;                      // the query's 32 lanes together
   const size_t wrows = (size_t(a.B) * a.H * a.NT - a.split_from) * a.split;
-  const float2* ml = reinterpret_cast<const float2*>(a.work + wrows * TT * kD);
-  float mm = -INFINITY;
-  for (int s = 0; s < a.split; ++s) {
-    const float2 v = ml[(size_t(row - a.split_from) * a.split + s) * TT + ql];
+  const float2* ml = reinterpret_cast<const float2*>(a.work + wrows * TT * kD) + size_t(k) * a.split * TT + ql;
+  const float4* op = reinterpret_cast<const float4*>(a.work + (size_t(k) * a.split * TT + ql) * kD) + ln;
+  float m[2], l[2], mm = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int s = ln + 32 * u;
+    const float2 v = s < a.split ? ml[size_t(s) * TT] : make_float2(-INFINITY, 0.f);
+    m[u] = v.x;
+    l[u] = v.y;
     if (v.y > 0.f) mm = fmaxf(mm, v.x);
   }
-  float acc[64];
 #pragma unroll
-  for (int d = 0; d < 64; ++d) acc[d] = 0.f;
-  float l = 0.f;
-  for (int s = 0; s < a.split; ++s) {
-    const size_t wrow = size_t(row - a.split_from) * a.split + s;
-    const float2 v = ml[wrow * TT + ql];
-    if (!(v.y > 0.f)) continue;   // empty slice
-    const float w = __builtin_amdgcn_exp2f(v.x - mm);
-    l += v.y * w;
-    const float4* op = reinterpret_cast<const float4*>(a.work + (wrow * TT + ql) * kD + 64 * half);
+  for (int o = 1; o < 32; o <<= 1) mm = fmaxf(mm, __shfl_xor(mm, o, 32));
+  float w[2], sum = 0.f;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      const float4 o = op[c];
-      acc[4 * c + 0] += o.x * w;
-      acc[4 * c + 1] += o.y * w;
-      acc[4 * c + 2] += o.z * w;
-      acc[4 * c + 3] += o.w * w;
+  for (int u = 0; u < 2; ++u) {
+    w[u] = l[u] > 0.f ? __builtin_amdgcn_exp2f(m[u] - mm) : 0.f;   // an empty slice weighs nothing
+    sum += w[u] * l[u];
+  }
+#pragma unroll
+  for (int o = 1; o < 32; o <<= 1) sum += __shfl_xor(sum, o, 32);
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int s0 = 0; s0 < a.split; s0 += 8) {
+    float4 v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = op[size_t(min(s0 + e, a.split - 1)) * TT * (kD / 4)];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int s = s0 + e;
+      const float f = __shfl(s < 32 ? w[0] : w[1], s & 31, 32);   // zero past the last slice
+      acc.x += f > 0.f ? v[e].x * f : 0.f;
+      acc.y += f > 0.f ? v[e].y * f : 0.f;
+      acc.z += f > 0.f ? v[e].z * f : 0.f;
+      acc.w += f > 0.f ? v[e].w * f : 0.f;
     }
   }
-  const float inv = (l > 0.f) ? 1.f / l : 0.f;
-  uint16_t* out = a.o + ((size_t(b) * a.L + qrow) * a.H + h) * kD + 64 * half;
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    uint4 w;
-    w.x = pack_bf16x2(acc[8 * c + 0] * inv, acc[8 * c + 1] * inv);
-    w.y = pack_bf16x2(acc[8 * c + 2] * inv, acc[8 * c + 3] * inv);
-    w.z = pack_bf16x2(acc[8 * c + 4] * inv, acc[8 * c + 5] * inv);
-    w.w = pack_bf16x2(acc[8 * c + 6] * inv, acc[8 * c + 7] * inv);
-    reinterpret_cast<uint4*>(out)[c] = w;
-  }
-  if (a.lse != nullptr && half == 0)
-    a.lse[(size_t(b) * a.H + h) * a.L + qrow] = (l > 0.f) ? (mm + log2f(l)) * 0.69314718055994531f : -INFINITY;
+  const float inv = (sum > 0.f) ? 1.f / sum : 0.f;
+  uint2 out;
+  out.x = pack_bf16x2(acc.x * inv, acc.y * inv);
+  out.y = pack_bf16x2(acc.z * inv, acc.w * inv);
+  *reinterpret_cast<uint2*>(a.o + ((size_t(b) * a.L + qrow) * a.H + h) * kD + 4 * ln) = out;
+  if (a.lse != nullptr && ln == 0)
+    a.lse[(size_t(b) * a.H + h) * a.L + qrow] = (sum > 0.f) ? (mm + log2f(sum)) * 0.69314718055994531f : -INFINITY;
 }
 
 }  // namespace
@@ -662,9 +673,9 @@ hipError_t launch_attn_split_merge(const AttnArgs& a, hipStream_t stream) {
   const unsigned rows = unsigned(a.B) * unsigned(a.H) * unsigned(a.NT) - unsigned(a.split_from);
   if (rows == 0) return hipSuccess;
   if (a.T == 128)
-    attn_split_merge_kernel<128><<<rows, 256, 0, stream>>>(a);
+    attn_split_merge_kernel<128><<<rows * (128 / kMergeQueries), 32 * kMergeQueries, 0, stream>>>(a);
   else
-    attn_split_merge_kernel<64><<<rows, 128, 0, stream>>>(a);
+    attn_split_merge_kernel<64><<<rows * (64 / kMergeQueries), 32 * kMergeQueries, 0, stream>>>(a);
   return hipGetLastError();
 }
 
