@@ -94,3 +94,25 @@ def test_lists_eviction_history_invariance():
     lb = b.gpu_lists(rule)
     for x, y in zip(la, lb):
         assert np.array_equal(x, y)
+
+
+def test_current_stream_and_views():
+    """Calls without a stream go to torch's current one, inside a stream context as
+    well; the list views are the buffer's sections, also of a larger buffer."""
+    P = require_gpu()
+    side = torch.cuda.Stream()
+    for ctx in (torch.cuda.stream(side), torch.cuda.stream(torch.cuda.default_stream())):
+        with ctx:
+            assert P._lib._stream_ptr(None) == torch.cuda.current_stream().cuda_stream
+    case = Case(P, 2, 300, 3, 128, 3, True, seed=77)
+    for _ in range(3):
+        case.append()
+    case.gpu_lists(case.rule(0.5))
+    lay = case.win.layout
+    big = torch.cat([case.win.lists, torch.zeros(256, dtype=torch.uint8, device="cuda")])
+    for views in (case.win.lists_views(), case.win.lists_views(big)):
+        for view, offset, shape in zip(views, (lay.counts_offset, lay.idx_offset, lay.mask_offset),
+                                       ((2, 3, 3), (2, 3, 3, lay.nk_cap), (2, 3, 3, lay.mask_words))):
+            n = int(np.prod(shape))
+            want = case.win.lists[offset:offset + 4 * n].view(torch.int32).view(shape)
+            assert view.is_contiguous() and torch.equal(view, want)
