@@ -214,7 +214,7 @@ __device__ inline RowTable row_table(int lane) {
 // of four units (s-1, s, s+1 and the one being copied), dO rows in a ring of
 // three, so that a unit is requested two phases before it is used.
 constexpr int kQRing = 4, kORing = 3, kLRing = 4;
-constexpr int kAhead = 6;   // operands in flight ahead of their product
+constexpr int kAhead = 4;   // operands in flight ahead of their product
 
 // The rows of a unit: W = T/16 waves fill UQ = T/2 rows of 256 bytes; copy i of
 // wave w fills LDS chunks [64*(W i + w), +64), rows 4(W i + w) + lane/16, whose
@@ -268,11 +268,11 @@ __global__ __launch_bounds__(4 * T, 2) void bwd_dkdv_kernel(BwdArgs a) {
 
   // the current chunk's tiles first: they (and the pinned chunk's, next at
   // position 0) are kept by every query tile and run longest
-  const int kj = blockIdx.x;
+  const int rows = a.B * a.H * a.NT;
+  const int order = int(blockIdx.x) / rows;
+  const int kj = xcd_item(int(blockIdx.x) - order * rows, rows, a.NT, T == 128 ? 256 : 512);
   const int t = kj % a.NT;
-  const int posbh = kj / a.NT;
-  const int bh = posbh % (a.B * a.H);
-  const int order = posbh / (a.B * a.H);
+  const int bh = kj / a.NT;
   const int pos = order == 0 ? a.n_live - 1 : order - 1;
   const int h = bh % a.H, b = bh / a.H;
   const int tid = threadIdx.x;
@@ -636,7 +636,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_kernel(BwdArgs a) {
   __shared__ uint4 sbuf[2][kUnit / 16];        // K 16 KB, V^T 16 KB
   __shared__ uint32_t sunit[2 * kDqList + 1];  // (key tile << 1) | half; the count last
 
-  const int row = blockIdx.x;                  // (b*H + h)*NT + i
+  const int row = xcd_item(int(blockIdx.x), int(gridDim.x), a.NT, 512);   // (b*H + h)*NT + i
   const int i = row % a.NT;
   const int bh = row / a.NT;
   const int h = bh % a.H, b = bh / a.H;

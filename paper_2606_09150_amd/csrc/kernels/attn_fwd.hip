@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_kernel(AttnArgs a) {
   __shared__ uint4 sbuf[3][kBuf / 16];             // K, K, V^T
   __shared__ uint32_t sunit[kList + 1];            // key tiles with a valid key; the count last
 
-  int row = int(blockIdx.x), part = 0;
+  int row = xcd_item(int(blockIdx.x), int(gridDim.x), a.NT, 3 * 256), part = 0;
   bool partial = false;
   if (SPLIT && row >= a.split_from) {
     const int k = row - a.split_from;

@@ -260,7 +260,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_tri_kernel(AttnArgs a) {
   __shared__ uint4 sbuf[kBuffers][kHalf / 16];
   __shared__ uint32_t sunit[UNITS ? kUnitCap + 1 : 1];   // (j << 1) | key half; the count last
 
-  int row = int(blockIdx.x), part = 0;
+  int row = xcd_item(int(blockIdx.x), int(gridDim.x), a.NT, 256), part = 0;
   bool partial = false;               // this workgroup writes a split-KV partial
   if (SPLIT && row >= a.split_from) {
     const int k = row - a.split_from;
