@@ -646,7 +646,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_kernel(BwdArgs a) {
   __shared__ uint4 sbuf[2][kUnit / 16];        // K 16 KB, V^T 16 KB
   __shared__ uint32_t sunit[2 * kDqList + 1];  // (key tile << 1) | half; the count last
 
-  const int row = xcd_item(int(blockIdx.x), int(gridDim.x), a.NT, 512);   // (b*H + h)*NT + i
+  const int row = xcd_item(int(blockIdx.x), a.B * a.H * a.NT, a.NT, 512);   // (b*H + h)*NT + i
   const int i = row % a.NT;
   const int bh = row / a.NT;
   const int h = bh % a.H, b = bh / a.H;
