@@ -28,7 +28,9 @@
 // as soon as the count is exact.  Every larger key is kept, then the first equal
 // ones (ties to the lower index), and the wave writes its row.
 //
-// What bounds them: pool_queries reads Q (75 MB at 1K, 18 us); the scores are
+// What bounds them: pool_queries reads Q (75 MB at 1K, 14.4 us, 5.2 TB/s, the
+// rate of a large copy; 17.8 us with a loop that had one load per lane in flight,
+// the lists 47.2 -> 42.4 us); the scores are
 // 2 x 128 unfused operations per pair (about 9 us of vector issue at 1K, 2,304
 // rows by 576 candidates); the selection is latency.  One kernel that scored two
 // query tiles against every candidate read each pooled key once per two rows (340
@@ -56,18 +58,25 @@ __device__ inline uint32_t order_key(float s) {
 
 template <int T>
 __global__ __launch_bounds__(kThreads) void pool_queries_kernel(TopkArgs a) {
-  __shared__ uint4 stage[T * (kD / 8)];
+  constexpr int kChunks = kD / 8;        // 16-byte chunks of a row
+  constexpr int kPer = T * kChunks / kThreads, kStep = kThreads / kChunks;
+  __shared__ uint4 stage[T * kChunks];
   const int row = blockIdx.x;            // (b*H + h)*NT + i
   const int i = row % a.NT;
   const int bh = row / a.NT;
   const int h = bh % a.H;
   const int b = bh / a.H;
   const int nv = tile_valid(a.tv, i, a.NT, a.tail, T);
-  for (int c = threadIdx.x; c < nv * (kD / 8); c += kThreads) {
-    const int r = c / (kD / 8);
-    const int cc = c - r * (kD / 8);
-    stage[c] = *reinterpret_cast<const uint4*>(a.q + ((size_t(b) * a.L + size_t(i) * T + r) * a.H + h) * kD + cc * 8);
-  }
+  // every load of the thread before any store to LDS; rows past the last valid
+  // one repeat it (and are not summed), so that no load has a branch
+  const int r0 = threadIdx.x / kChunks, cc = threadIdx.x % kChunks;
+  uint4 chunk[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k)
+    chunk[k] = *reinterpret_cast<const uint4*>(
+        a.q + ((size_t(b) * a.L + size_t(i) * T + min(r0 + kStep * k, nv - 1)) * a.H + h) * kD + cc * 8);
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) stage[(r0 + kStep * k) * kChunks + cc] = chunk[k];
   __syncthreads();
   if (threadIdx.x < kD) {
     const uint16_t* st = reinterpret_cast<const uint16_t*>(stage);

@@ -108,6 +108,19 @@ def test_topk_selection_sizes(chunks, nt):
         _topk_compare(case, q, oracle.TopkRule(budget, False, False))
 
 
+# the last tile's row count around the pooling kernel's 16 rows per pass (its loads
+# past the last valid row repeat that row); lists against the oracle, bit for bit
+@pytest.mark.parametrize("T", [64, 128])
+@pytest.mark.parametrize("tail", [1, 15, 16, 17, 63])
+def test_topk_pooled_query_tails(T, tail):
+    P = require_gpu()
+    log(f"topk query tail T={T} tail={tail}")
+    case = Case(P, 1, 3 * T + tail, 2, T, 3, False, seed=4700 + tail, gen_device="cuda")
+    for _ in range(3):
+        case.append()
+    _topk_compare(case, case.query(), oracle.TopkRule(3))
+
+
 @pytest.mark.parametrize("name,frac", [("1k", 0.25), ("2k", 0.15)])
 def test_topk_lists_workloads(name, frac):
     """Full-size windows in the bench's configuration, every head, bit for bit."""
