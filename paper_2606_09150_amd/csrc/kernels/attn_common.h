@@ -2,6 +2,7 @@
 #pragma once
 
 #include "../launch.h"
+#include "../xcd_order.h"
 
 namespace uf {
 namespace attn {
@@ -59,21 +60,6 @@ __device__ __forceinline__ const uint8_t* uniform_ptr(const uint8_t* q) {
   const uint64_t lo = uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(p)));
   const uint64_t hi = uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(p >> 32)));
   return reinterpret_cast<const uint8_t*>(lo | (hi << 32));
-}
-
-// Workgroups are dealt to the 8 XCDs in turn.  Where those resident at once span
-// several heads (NT rows each), item i of n becomes one of a contiguous range of
-// items per XCD (equal ranges up to one item), so that an XCD's workgroups stream
-// the same head's tiles through its L2.  With a head's rows more than a quarter
-// of the resident workgroups the order stays: every XCD streams one or two heads
-// anyway.  12 heads, against the order of the grid: 73 tiles of 64 tokens 484 -> 462
-// us, 37 tiles of 128 503 -> 496 us, backward of the latter 1685 -> 1672 us, of 12 x 2
-// heads and 24 tiles of 64 183 -> 177.5 us; at 192 tiles of 128 the forward was 0 to
-// 2 % slower, depending on the card.
-__device__ __forceinline__ int xcd_item(int i, int n, int NT, int resident) {
-  if (NT * 4 > resident) return i;
-  const int x = i & 7, k = i >> 3, q = n >> 3, r = n & 7;
-  return x * q + min(x, r) + k;
 }
 
 // s_waitcnt immediates (gfx9 encoding): vmcnt in [3:0] and [15:14], expcnt

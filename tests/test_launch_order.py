@@ -1,0 +1,51 @@
+"""The order in which an attention launch's workgroups take rows and slices:
+csrc/xcd_order.h compiled for the host and read back, workgroup by workgroup."""
+
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2606_09150_amd", "csrc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "xcd_order.h"
+int main(int, char** v) {
+  const int n = atoi(v[1]), whole = atoi(v[2]), nt = atoi(v[3]), resident = atoi(v[4]);
+  for (int i = 0; i < n; ++i) printf("%d\n", uf::xcd_split_item(i, n, whole, nt, resident));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def order(tmp_path_factory):
+    d = tmp_path_factory.mktemp("order")
+    (d / "order.cpp").write_text(PROGRAM)
+    exe = str(d / "order")
+    subprocess.run(["g++", "-std=c++17", f"-I{CSRC}", str(d / "order.cpp"), "-o", exe], check=True)
+    return lambda *args: [int(x) for x in subprocess.check_output([exe, *map(str, args)]).split()]
+
+
+# (rows, rows kept whole, slices of each other row, rows of a head, resident workgroups)
+@pytest.mark.parametrize("rows,whole,split,nt,resident", [
+    (444, 256, 4, 37, 256), (304, 256, 5, 19, 256), (456, 256, 5, 19, 256), (36, 20, 3, 6, 256), (36, 13, 7, 6, 768),
+    (444, 0, 4, 37, 256), (444, 444, 1, 37, 256), (5, 0, 51, 5, 256), (2304, 2048, 2, 192, 256), (300, 299, 64, 25, 768)])
+def test_whole_rows_and_slices_are_dealt_alike_to_every_xcd(order, rows, whole, split, nt, resident):
+    n = whole + (rows - whole) * split
+    items = order(n, whole, nt, resident)
+    assert sorted(items) == list(range(n))
+    assert all(x < whole for x in items[:whole])                 # whole rows start first
+    on_xcd = [items[x::8] for x in range(8)]                     # workgroup i runs on XCD i % 8
+    for kind in (lambda it: it < whole, lambda it: it >= whole):
+        share = [sum(map(kind, it)) for it in on_xcd]
+        assert max(share) - min(share) <= 1
+    # the XCDs' loads, in row-times, differ by at most a row and a slice
+    load = [sum(1.0 if i < whole else 1.0 / split for i in it) for it in on_xcd]
+    assert max(load) - min(load) <= 1.0 + 1.0 / split
+    if nt * 4 <= resident:                                       # and its items of a kind are neighbours
+        for it in on_xcd:
+            for kind in ([i for i in it if i < whole], [i for i in it if i >= whole]):
+                assert not kind or kind == list(range(kind[0], kind[0] + len(kind)))
