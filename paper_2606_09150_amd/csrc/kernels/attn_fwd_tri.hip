@@ -617,8 +617,10 @@ __global__ __launch_bounds__(32 * kMergeQueries) void attn_split_merge_kernel(At
   float w[2], sum = 0.f;
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    w[u] = l[u] > 0.f ? __builtin_amdgcn_exp2f(m[u] - mm) : 0.f;   // an empty slice weighs nothing
-    sum += w[u] * l[u];
+    // an empty slice is left out (weight -1); one whose weight underflows is not,
+    // so that its infinities and NaN reach O as they do without a split
+    w[u] = l[u] > 0.f ? __builtin_amdgcn_exp2f(m[u] - mm) : -1.f;
+    if (l[u] > 0.f) sum += w[u] * l[u];
   }
 #pragma unroll
   for (int o = 1; o < 32; o <<= 1) sum += __shfl_xor(sum, o, 32);
@@ -630,11 +632,11 @@ __global__ __launch_bounds__(32 * kMergeQueries) void attn_split_merge_kernel(At
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int s = s0 + e;
-      const float f = __shfl(s < 32 ? w[0] : w[1], s & 31, 32);   // zero past the last slice
-      acc.x += f > 0.f ? v[e].x * f : 0.f;
-      acc.y += f > 0.f ? v[e].y * f : 0.f;
-      acc.z += f > 0.f ? v[e].z * f : 0.f;
-      acc.w += f > 0.f ? v[e].w * f : 0.f;
+      const float f = __shfl(s < 32 ? w[0] : w[1], s & 31, 32);   // -1 past the last slice
+      acc.x += f < 0.f ? 0.f : v[e].x * f;
+      acc.y += f < 0.f ? 0.f : v[e].y * f;
+      acc.z += f < 0.f ? 0.f : v[e].z * f;
+      acc.w += f < 0.f ? 0.f : v[e].w * f;
     }
   }
   const float inv = (sum > 0.f) ? 1.f / sum : 0.f;

@@ -584,6 +584,27 @@ def test_tiny_workload_split_rows():
     assert err <= REL_TOL and lerr <= lse_tol(64)
 
 
+# Two chunks whose logits differ by 2 * 128 * 8 / sqrt(128) = 181 (261 in base 2): the
+# older one's weights underflow to zero, and its infinite V gives 0 * inf = NaN,
+# whether its keys share a workgroup with the others or are a slice of their own.
+@pytest.mark.parametrize("T", [64, 128])
+def test_split_keeps_nan_of_underflowed_slices(T):
+    P = require_gpu()
+    log(f"attn split underflow T={T}")
+    win = P.KVWindow(1, 2, T, T, 2, False)
+    ones = torch.ones((1, T, 2, 128), dtype=torch.bfloat16, device="cuda")
+    v = ones.clone()
+    v[0, 5, :, 3] = math.inf
+    win.append(-ones, v)
+    win.append(ones, ones)
+    win.build_lists(1, 1.0)
+    for split in (None, 2):
+        o, _ = win.attention(8 * ones, split=split)
+        nan = torch.isnan(o)
+        assert nan[..., 3].all() and nan.sum() == nan[..., 3].sum()
+        assert (o[~nan] == 1).all()
+
+
 def test_plan_chosen_split_long_window_few_rows():
     """A window of 32 chunks whose 5 rows (one head, 5 query tiles) fill few
     CUs: the plan cuts every row into 51 slices, and the attention with
