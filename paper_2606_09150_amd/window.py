@@ -115,7 +115,10 @@ class KVWindow:
         nt = -(-self.L // self.T)
         # one reinterpretation and a strided view per section (7 -> 4 us a call
         # against a slice, a reinterpretation and a reshape for each)
-        words = buf[:lay.total_bytes].view(torch.int32)
+        end = lay.mask_offset + 4 * lay.rows * lay.mask_words
+        if buf.dim() != 1 or buf.element_size() != 1 or buf.numel() < end:   # as_strided looks past the buffer
+            raise ValueError(f"list buffer must be {end} bytes or more, in one dimension")
+        words = buf[:end].view(torch.int32)
         at = words.storage_offset()
 
         def section(offset, n, *shape):

@@ -300,6 +300,26 @@ def test_backward_host_paths(P):
     assert "1008 rows" in L.uf_last_error()
 
 
+def test_lists_views_stay_within_their_buffer(P):
+    """Views of a buffer of the lists' size, also inside a larger one; a shorter
+    piece, other element sizes and more dimensions are refused."""
+    import torch
+    w = _dry(P, max_chunks=3, L=300, T=128, H=3, B=2)
+    lay = w.layout
+    end = lay.mask_offset + 4 * lay.rows * lay.mask_words
+    big = torch.zeros(2 * lay.total_bytes + 64, dtype=torch.uint8)
+    for buf in (big[:lay.total_bytes], big[64:64 + end], big[64:64 + end + 2], big.view(torch.int8)[:lay.total_bytes]):
+        views = w.lists_views(buf)
+        assert [tuple(v.shape) for v in views] == [(2, 3, 3), (2, 3, 3, lay.nk_cap), (2, 3, 3, lay.mask_words)]
+        for v, offset in zip(views, (lay.counts_offset, lay.idx_offset, lay.mask_offset)):
+            assert v.data_ptr() == buf.data_ptr() + offset and v.is_contiguous() and v.dtype == torch.int32
+    whole = big[:lay.total_bytes]
+    for buf in (big[:end - 4], big[64:64 + lay.idx_offset], whole.view(torch.int32), big.view(torch.int32),
+                big.view(2, -1), big[1:1 + end], big[::2]):
+        with pytest.raises((ValueError, RuntimeError)):
+            w.lists_views(buf)
+
+
 def test_tail_plan_and_split_rows_host_paths(P):
     L = P._lib
     E = P.UfError
