@@ -4,8 +4,8 @@
 // and beyond nk).  A wave ballot gives two 32-bit mask words; the kept indices
 // are placed in ascending order, and the tail of the row is padded with -1.
 // A wave per row needs no barrier (four rows run side by side in a workgroup);
-// a workgroup per row takes 256 tiles per pass with two barriers, and is for the
-// longest rows.
+// a workgroup per row takes 256 tiles per pass with two barriers, and is for few
+// or long rows (list_rule.h) and top-k rows of more than 4,096 candidates.
 #pragma once
 
 #include "../launch.h"

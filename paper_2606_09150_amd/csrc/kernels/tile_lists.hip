@@ -7,8 +7,10 @@
 // key tile kept iff the upper 32 bits of a SplitMix64 chain over
 // (b, h, seq(current), i, seq(chunk), t) fall below floor(p * 2^32).
 //
-// One wave per list row, four rows per workgroup; the row is written by the
-// shared output stage (list_emit.h).  Integer-only, so the lists are bit-exact.
+// One wave per list row, four rows per workgroup, or a workgroup per row
+// (list_rule.h); the row is written by the shared output stage (list_emit.h).
+// Integer-only, so the lists are bit-exact.
+#include "../list_rule.h"
 #include "list_emit.h"
 
 namespace uf {
@@ -26,20 +28,22 @@ __device__ inline uint64_t splitmix64(uint64_t z) {
   return z ^ (z >> 31);
 }
 
+template <bool WAVE>
 __global__ __launch_bounds__(kThreads) void tile_lists_kernel(ListArgs a) {
   // the chunks' sequence numbers, and whether the rule keeps them whole, in LDS:
   // indexed by a lane's tile, kernel arguments are vector loads from memory
   // that is not cached, one round trip per 256 tiles
   __shared__ uint64_t sseq[UF_MAX_CHUNKS];
   __shared__ int sforced[UF_MAX_CHUNKS];
+  __shared__ int wave_count[kWaves];
   if (threadIdx.x < UF_MAX_CHUNKS) {
     const int p = threadIdx.x;
     sseq[p] = uint64_t(a.seq[p]);
     sforced[p] = (a.sink[p] && a.keep_sink) || (a.seq[p] == a.cur_seq && a.keep_current);
   }
   __syncthreads();
-  const int row = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (row >= a.rows) return;
+  const int row = WAVE ? blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : blockIdx.x;
+  if (row >= a.rows) return;                 // WAVE only: whole waves, and no barrier follows
   const int i = row % a.NT;
   const int bh = row / a.NT;
   const int h = bh % a.H;
@@ -64,13 +68,19 @@ __global__ __launch_bounds__(kThreads) void tile_lists_kernel(ListArgs a) {
     y = splitmix64(y ^ uint64_t(t));
     return (y >> 32) < a.thr;
   };
-  lists::emit_row_wave(keep_of, a.nk_cap, a.mask_words, counts + row, idx, mask);
+  if constexpr (WAVE)
+    lists::emit_row_wave(keep_of, a.nk_cap, a.mask_words, counts + row, idx, mask);
+  else
+    lists::emit_row(keep_of, a.nk_cap, a.mask_words, counts + row, idx, mask, wave_count);
 }
 
 }  // namespace
 
 hipError_t launch_tile_lists(const ListArgs& a, hipStream_t stream) {
-  tile_lists_kernel<<<unsigned(a.rows + kWaves - 1) / kWaves, kThreads, 0, stream>>>(a);
+  if (lists_wave_per_row(a.rows, a.nk_cap))
+    tile_lists_kernel<true><<<unsigned(a.rows + kWaves - 1) / kWaves, kThreads, 0, stream>>>(a);
+  else
+    tile_lists_kernel<false><<<unsigned(a.rows), kThreads, 0, stream>>>(a);
   return hipGetLastError();
 }
 

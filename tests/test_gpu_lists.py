@@ -50,6 +50,18 @@ def test_lists_bit_exact_workloads(name):
         assert bits.all()
 
 
+# A wave per row (768 rows or more, rows at most 5/8 as long as there are rows) and a
+# workgroup per row: both sides of either limit, rows of ragged lengths.
+@pytest.mark.parametrize("H,nt,chunks", [(12, 64, 2), (13, 59, 3), (16, 49, 9), (16, 49, 11), (1, 65, 64)])
+def test_lists_bit_exact_row_splits(H, nt, chunks):
+    P = require_gpu()
+    log(f"lists rows={H * nt} tiles={nt * chunks}")
+    case = ZeroCase(P, 1, nt * 64 - 5, H, 64, chunks, True, 4200 + nt)
+    for _ in range(chunks):
+        case.append()
+    _compare(case, case.rule(0.3))
+
+
 def test_lists_stream_steps():
     P = require_gpu()
     wl = synth.WORKLOADS["1k_stream"]

@@ -1,5 +1,6 @@
-"""The order in which an attention launch's workgroups take rows and slices:
-csrc/xcd_order.h compiled for the host and read back, workgroup by workgroup."""
+"""Rules of the launches, compiled for the host and read back: the order in which
+an attention launch's workgroups take rows and slices (csrc/xcd_order.h), and how
+many lanes a list row gets (csrc/list_rule.h)."""
 
 import os
 import subprocess
@@ -12,8 +13,10 @@ CSRC = os.path.join(ROOT, "paper_2606_09150_amd", "csrc")
 PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
+#include "list_rule.h"
 #include "xcd_order.h"
-int main(int, char** v) {
+int main(int c, char** v) {
+  if (c == 3) return printf("%d\n", int(uf::lists_wave_per_row(atoi(v[1]), atoi(v[2])))) < 0;
   const int n = atoi(v[1]), whole = atoi(v[2]), nt = atoi(v[3]), resident = atoi(v[4]);
   for (int i = 0; i < n; ++i) printf("%d\n", uf::xcd_split_item(i, n, whole, nt, resident));
 }
@@ -21,7 +24,7 @@ int main(int, char** v) {
 
 
 @pytest.fixture(scope="module")
-def order(tmp_path_factory):
+def rules(tmp_path_factory):
     d = tmp_path_factory.mktemp("order")
     (d / "order.cpp").write_text(PROGRAM)
     exe = str(d / "order")
@@ -33,9 +36,9 @@ def order(tmp_path_factory):
 @pytest.mark.parametrize("rows,whole,split,nt,resident", [
     (444, 256, 4, 37, 256), (304, 256, 5, 19, 256), (456, 256, 5, 19, 256), (36, 20, 3, 6, 256), (36, 13, 7, 6, 768),
     (444, 0, 4, 37, 256), (444, 444, 1, 37, 256), (5, 0, 51, 5, 256), (2304, 2048, 2, 192, 256), (300, 299, 64, 25, 768)])
-def test_whole_rows_and_slices_are_dealt_alike_to_every_xcd(order, rows, whole, split, nt, resident):
+def test_whole_rows_and_slices_are_dealt_alike_to_every_xcd(rules, rows, whole, split, nt, resident):
     n = whole + (rows - whole) * split
-    items = order(n, whole, nt, resident)
+    items = rules(n, whole, nt, resident)
     assert sorted(items) == list(range(n))
     assert all(x < whole for x in items[:whole])                 # whole rows start first
     on_xcd = [items[x::8] for x in range(8)]                     # workgroup i runs on XCD i % 8
@@ -49,3 +52,12 @@ def test_whole_rows_and_slices_are_dealt_alike_to_every_xcd(order, rows, whole, 
         for it in on_xcd:
             for kind in ([i for i in it if i < whole], [i for i in it if i >= whole]):
                 assert not kind or kind == list(range(kind[0], kind[0] + len(kind)))
+
+
+# (rows, key tiles of a row, a wave per row): where one side was at least 4 % faster
+@pytest.mark.parametrize("rows,nk,wave", [
+    (52, 156, 0), (64, 512, 0), (64, 4096, 0), (195, 12480, 0), (338, 1352, 0), (768, 1024, 0), (768, 4096, 0),
+    (1014, 1352, 0), (2304, 2048, 0), (2340, 12480, 0), (777, 148, 1), (1752, 292, 1), (1575, 700, 1), (2400, 960, 1),
+    (4056, 1352, 1), (7680, 960, 1), (8970, 12480, 1)])
+def test_few_or_long_list_rows_get_a_workgroup(rules, rows, nk, wave):
+    assert rules(rows, nk) == [wave]
