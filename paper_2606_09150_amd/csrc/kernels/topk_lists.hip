@@ -37,6 +37,11 @@
 // MB from L2) and selected with histograms in two of its four waves: 66 us for
 // what topk_scores and topk_select now do in 15 + 13 us.  Windows with few
 // rows and candidates take two kernels: topk_select computes its row's keys.
+// (That form was slower than the one kernel where rows were few, as a workgroup held
+// four rows and a wave all candidates of one, eight chunks of their keys in flight:
+// 8 rows x 124 candidates 15.3 us in one kernel, then 18.5, and 14.5 with a workgroup
+// per row and a wave per 64 candidates.)
+#include "../list_rule.h"
 #include "list_emit.h"
 
 #pragma clang fp contract(off)
@@ -152,11 +157,16 @@ __global__ __launch_bounds__(kThreads) void topk_scores_kernel(TopkArgs a) {
 
 // W waves per row, K keys per lane (64 W K >= candidates).  RANK: the budget
 // cuts the candidates (otherwise all of them are kept, or none).  SCORE: the
-// row's wave computes its keys itself (a lane takes a candidate) instead of
-// reading those of topk_scores.
-template <int W, int K, bool RANK, bool SCORE>
-__global__ __launch_bounds__(kThreads) void topk_select_kernel(TopkArgs a) {
-  constexpr int kRows = kWaves / W;        // rows of a workgroup
+// row's waves compute its keys themselves (a lane takes a candidate) instead of
+// reading those of topk_scores; ALONE: each row in a workgroup of its own, so
+// that few rows spread over as many CUs, and a lane requests its candidate's
+// whole pooled key (512 bytes) before it uses any of it.
+enum Keys { kRead, kScore, kScoreAlone };
+template <int W, int K, bool RANK, Keys KEYS>
+__global__ __launch_bounds__(KEYS == kScoreAlone ? 64 * W : kThreads) void topk_select_kernel(TopkArgs a) {
+  constexpr bool SCORE = KEYS != kRead, ALONE = KEYS == kScoreAlone;
+  static_assert(!SCORE || (RANK && (ALONE ? K == 1 : W == 1)), "rows scored in place");
+  constexpr int kRows = ALONE ? 1 : kWaves / W;   // rows of a workgroup
   constexpr int kWords = W * K;            // 64-candidate words of a row
   __shared__ uint64_t sgt[RANK ? kRows : 1][RANK ? kWords : 1], seq[RANK ? kRows : 1][RANK ? kWords : 1];
   __shared__ int part[2][kWaves];
@@ -174,33 +184,42 @@ __global__ __launch_bounds__(kThreads) void topk_select_kernel(TopkArgs a) {
     if constexpr (SCORE) {
       __shared__ float4 sqm[kRows][kD / 4];
       const int bh = row / a.NT;
-      if (lane < kD / 4)
+      if (lane < kD / 4)                     // (every wave of the row writes the same)
         sqm[slot][lane] = reinterpret_cast<const float4*>(a.lists + a.scratch_offset)[size_t(row) * (kD / 4) + lane];
-      __builtin_amdgcn_wave_barrier();
+      if constexpr (W > 1) __syncthreads();
+      else __builtin_amdgcn_wave_barrier();
       const float4* kp[K];
       float acc[K];
 #pragma unroll
       for (int i = 0; i < K; ++i) {
-        const int j = a.cand_lo + min(64 * i + lane, nc - 1);
+        const int j = a.cand_lo + min(64 * (sub + W * i) + lane, nc - 1);
         const int pos = j / a.NT;
         kp[i] = reinterpret_cast<const float4*>(a.kmean) +
                 (size_t(a.slot_of[pos]) * a.B * a.H * a.NT + size_t(bh) * a.NT + (j - pos * a.NT)) * (kD / 4);
         acc[i] = 0.f;
       }
-#pragma unroll 8
-      for (int c = 0; c < kD / 4; ++c) {
-        const float4 q = sqm[slot][c];
+      constexpr int kAhead = ALONE ? kD / 4 : 8;   // chunks requested at a time
+#pragma unroll 1
+      for (int c0 = 0; c0 < kD / 4; c0 += kAhead) {
+        float4 k[K][kAhead];
 #pragma unroll
-        for (int i = 0; i < K; ++i) {
-          const float4 k = kp[i][c];
-          acc[i] = acc[i] + q.x * k.x;
-          acc[i] = acc[i] + q.y * k.y;
-          acc[i] = acc[i] + q.z * k.z;
-          acc[i] = acc[i] + q.w * k.w;
+        for (int c = 0; c < kAhead; ++c)
+#pragma unroll
+          for (int i = 0; i < K; ++i) k[i][c] = kp[i][c0 + c];
+#pragma unroll
+        for (int c = 0; c < kAhead; ++c) {
+          const float4 q = sqm[slot][c0 + c];
+#pragma unroll
+          for (int i = 0; i < K; ++i) {
+            acc[i] = acc[i] + q.x * k[i][c].x;
+            acc[i] = acc[i] + q.y * k[i][c].y;
+            acc[i] = acc[i] + q.z * k[i][c].z;
+            acc[i] = acc[i] + q.w * k[i][c].w;
+          }
         }
       }
 #pragma unroll
-      for (int i = 0; i < K; ++i) key[i] = 64 * i + lane < nc ? order_key(acc[i]) : 0u;
+      for (int i = 0; i < K; ++i) key[i] = 64 * (sub + W * i) + lane < nc ? order_key(acc[i]) : 0u;
     } else {
 #pragma unroll
       for (int i = 0; i < K; ++i) {
@@ -283,6 +302,7 @@ __global__ __launch_bounds__(kThreads) void topk_select_kernel(TopkArgs a) {
     else __builtin_amdgcn_wave_barrier();
   }
 
+  if (ALONE && sub != 0) return;           // the first wave writes the row; no barrier follows
   const int qi = row % a.NT;
   auto keep_of = [&](int j) {
     if (j >= a.nk) return false;
@@ -294,7 +314,7 @@ __global__ __launch_bounds__(kThreads) void topk_select_kernel(TopkArgs a) {
   };
   int32_t* count = reinterpret_cast<int32_t*>(a.lists) + row;
   uint32_t* mask = reinterpret_cast<uint32_t*>(a.lists + a.mask_offset) + size_t(row) * a.mask_words;
-  if constexpr (W == 1)
+  if constexpr (W == 1 || ALONE)
     lists::emit_row_wave(keep_of, a.nk_cap, a.mask_words, count, idx, mask);
   else
     lists::emit_row(keep_of, a.nk_cap, a.mask_words, count, idx, mask, part[0]);
@@ -308,7 +328,7 @@ hipError_t launch_topk_lists(const TopkArgs& a, hipStream_t stream) {
   hipError_t e = hipSuccess;
   // a budget of none or of every candidate needs no score
   if (a.budget == 0 || a.budget >= nc) {
-    topk_select_kernel<1, 1, false, false><<<(rows + 3) / 4, kThreads, 0, stream>>>(a);
+    topk_select_kernel<1, 1, false, kRead><<<(rows + 3) / 4, kThreads, 0, stream>>>(a);
     return hipGetLastError();
   }
   if (a.T == 128)
@@ -318,24 +338,31 @@ hipError_t launch_topk_lists(const TopkArgs& a, hipStream_t stream) {
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const unsigned four = (rows + 3) / 4;
   // Few pairs: a launch costs more than reading each pooled key once per row.
-  // Two launches against three: 20 rows x 20 candidates 11 against 15 us, 720 x
-  // 60 13 against 16.5, 1,024 x 64 16 against 18; 720 x 120 17.7 against 17.3,
-  // 2,560 x 64 33.6 against 30.7.
-  if (nc <= 64 * 2 && uint64_t(rows) * uint64_t(nc) <= 80000) {
-    if (nc <= 64) topk_select_kernel<1, 1, true, true><<<four, kThreads, 0, stream>>>(a);
-    else topk_select_kernel<1, 2, true, true><<<four, kThreads, 0, stream>>>(a);
+  const unsigned waves = unsigned(nc + 63) / 64;
+  if (topk_row_alone(int(rows), nc)) {
+    if (waves == 1) topk_select_kernel<1, 1, true, kScoreAlone><<<rows, 64, 0, stream>>>(a);
+    else if (waves == 2) topk_select_kernel<2, 1, true, kScoreAlone><<<rows, 128, 0, stream>>>(a);
+    else topk_select_kernel<4, 1, true, kScoreAlone><<<rows, 256, 0, stream>>>(a);
+    return hipGetLastError();
+  }
+  // More rows of few candidates, four to a workgroup; two launches against three:
+  // 1,500 rows x 50 21.6 against 23.1 us, 4,000 x 20 34.7 against 36.1, 640 x 120
+  // 16.4 against 16.7; 960 x 120 18.5 either way, 2,560 x 64 28.5 either way.
+  if (waves <= 2 && uint64_t(rows) * uint64_t(nc) <= 80000) {
+    if (waves == 1) topk_select_kernel<1, 1, true, kScore><<<four, kThreads, 0, stream>>>(a);
+    else topk_select_kernel<1, 2, true, kScore><<<four, kThreads, 0, stream>>>(a);
     return hipGetLastError();
   }
   const unsigned tiles = (unsigned(a.NT + kTile - 1) / kTile) * (unsigned(nc + kTile - 1) / kTile);
   topk_scores_kernel<<<tiles * unsigned(a.B) * unsigned(a.H), kThreads, 0, stream>>>(a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // keys per lane: the fewest that hold a row; past 64 a row takes four waves
-  if (nc <= 64 * 4) topk_select_kernel<1, 4, true, false><<<four, kThreads, 0, stream>>>(a);
-  else if (nc <= 64 * 10) topk_select_kernel<1, 10, true, false><<<four, kThreads, 0, stream>>>(a);
-  else if (nc <= 64 * 16) topk_select_kernel<1, 16, true, false><<<four, kThreads, 0, stream>>>(a);
-  else if (nc <= 64 * 32) topk_select_kernel<1, 32, true, false><<<four, kThreads, 0, stream>>>(a);
-  else if (nc <= 64 * 64) topk_select_kernel<1, 64, true, false><<<four, kThreads, 0, stream>>>(a);
-  else topk_select_kernel<4, 64, true, false><<<rows, kThreads, 0, stream>>>(a);
+  if (nc <= 64 * 4) topk_select_kernel<1, 4, true, kRead><<<four, kThreads, 0, stream>>>(a);
+  else if (nc <= 64 * 10) topk_select_kernel<1, 10, true, kRead><<<four, kThreads, 0, stream>>>(a);
+  else if (nc <= 64 * 16) topk_select_kernel<1, 16, true, kRead><<<four, kThreads, 0, stream>>>(a);
+  else if (nc <= 64 * 32) topk_select_kernel<1, 32, true, kRead><<<four, kThreads, 0, stream>>>(a);
+  else if (nc <= 64 * 64) topk_select_kernel<1, 64, true, kRead><<<four, kThreads, 0, stream>>>(a);
+  else topk_select_kernel<4, 64, true, kRead><<<rows, kThreads, 0, stream>>>(a);
   return hipGetLastError();
 }
 

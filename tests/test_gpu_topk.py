@@ -90,9 +90,9 @@ def test_topk_lists_bit_exact(B, L, H, T, mc, pin, n, budget, keep_sink, keep_cu
     _topk_compare(case, case.query(), oracle.TopkRule(budget, keep_sink, keep_current))
 
 
-# The selection holds a row's keys in 1 or 2 (few pairs, scored in place), 4, 10,
-# 16, 32 or 64 registers per lane, then in four waves: candidate counts at both
-# sides of each limit.  With the same keys
+# The selection holds a row's keys in 1 register of one, two or four waves (few pairs,
+# scored in place), in 4, 10, 16, 32 or 64 registers per lane, then in four waves:
+# candidate counts at both sides of each limit.  With the same keys
 # in every chunk each score occurs once per chunk, so the budget cuts through ties.
 @pytest.mark.parametrize("chunks,nt", [(2, 32), (5, 13), (2, 64), (3, 43), (4, 64), (1, 257), (10, 64), (1, 641), (16, 64), (25, 41), (32, 64), (3, 683),
                                        (64, 64), (17, 241)])
@@ -106,6 +106,19 @@ def test_topk_selection_sizes(chunks, nt):
     q = case._draw(1, "q")
     for budget in (1, chunks * nt // 3 + 1, chunks * nt - 1):
         _topk_compare(case, q, oracle.TopkRule(budget, False, False))
+
+
+# Rows scored in place: the most that get a workgroup each (one, two and four waves), and
+# four to a workgroup beyond (one and two candidates to a lane).
+@pytest.mark.parametrize("H,chunks,nt", [(16, 1, 64), (20, 1, 52), (8, 2, 64), (16, 1, 65), (10, 2, 53), (4, 4, 64)])
+def test_topk_rows_scored_in_place(H, chunks, nt):
+    P = require_gpu()
+    log(f"topk in place rows={H * nt} candidates={chunks * nt}")
+    case = Case(P, 1, nt * 64 - 3, H, 64, chunks, True, seed=4300 + nt, gen_device="cuda")
+    for _ in range(chunks):
+        case.append()
+        case.n_appended = 0
+    _topk_compare(case, case._draw(1, "q"), oracle.TopkRule(chunks * nt // 3 + 1, False, False))
 
 
 # the last tile's row count around the pooling kernel's 16 rows per pass (its loads

@@ -16,6 +16,7 @@ PROGRAM = r"""
 #include "list_rule.h"
 #include "xcd_order.h"
 int main(int c, char** v) {
+  if (c == 4) return printf("%d\n", int(uf::topk_row_alone(atoi(v[2]), atoi(v[3])))) < 0;
   if (c == 3) return printf("%d\n", int(uf::lists_wave_per_row(atoi(v[1]), atoi(v[2])))) < 0;
   const int n = atoi(v[1]), whole = atoi(v[2]), nt = atoi(v[3]), resident = atoi(v[4]);
   for (int i = 0; i < n; ++i) printf("%d\n", uf::xcd_split_item(i, n, whole, nt, resident));
@@ -61,3 +62,11 @@ def test_whole_rows_and_slices_are_dealt_alike_to_every_xcd(rules, rows, whole, 
     (4056, 1352, 1), (7680, 960, 1), (8970, 12480, 1)])
 def test_few_or_long_list_rows_get_a_workgroup(rules, rows, nk, wave):
     assert rules(rows, nk) == [wave]
+
+
+# (rows, ranked candidates, a workgroup per row): where one side was at least 4 % faster
+@pytest.mark.parametrize("rows,nc,alone", [
+    (4, 62, 1), (8, 124, 1), (592, 37, 1), (732, 61, 1), (512, 96, 1), (12, 186, 1), (250, 250, 1), (256, 160, 1),
+    (2560, 64, 0), (800, 100, 0), (960, 120, 0), (320, 240, 0), (444, 148, 0), (480, 240, 0), (1, 257, 0)])
+def test_few_topk_rows_get_a_workgroup(rules, rows, nc, alone):
+    assert rules("topk", rows, nc) == [alone]
