@@ -5,7 +5,7 @@
 // are placed in ascending order, and the tail of the row is padded with -1.
 // A wave per row needs no barrier (four rows run side by side in a workgroup);
 // a workgroup per row takes 256 tiles per pass with two barriers, and is for few
-// or long rows (list_rule.h) and top-k rows of more than 4,096 candidates.
+// or long rows (list_rule.h) and top-k rows of more than 2,048 candidates.
 #pragma once
 
 #include "../launch.h"

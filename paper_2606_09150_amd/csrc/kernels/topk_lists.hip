@@ -356,12 +356,19 @@ hipError_t launch_topk_lists(const TopkArgs& a, hipStream_t stream) {
   const unsigned tiles = (unsigned(a.NT + kTile - 1) / kTile) * (unsigned(nc + kTile - 1) / kTile);
   topk_scores_kernel<<<tiles * unsigned(a.B) * unsigned(a.H), kThreads, 0, stream>>>(a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  // keys per lane: the fewest that hold a row; past 64 a row takes four waves
+  // Keys per lane: every one that a row does not need costs 0.2 to 0.8 us (2,304 rows
+  // of 384: 6 keys 35.9 us, 8 36.4, 10 37.2, 16 39.3; of 576: 10 42.3, 12 42.8, 16 44.5; 444
+  // of 222: 4 18.1, 10 21.1), so a few steps; 10 serves 257 to 640 candidates.  32 keys
+  // spill 53 scalar registers (the ballots) and are still the better form of many rows:
+  // 3,000 rows of 1,500 86 us, four waves of 8 keys 92, of 16 keys 105 (500 rows: 42, 31 and 34).
+  // Past 2,048 a row takes four waves: against one of 64 keys, which spill 207, 250 rows of
+  // 3,000 32.5 and 64.8 us, 1,000 of 4,000 71 and 96, 3,000 of 3,000 141 and 147.  Four waves of
+  // 64 keys take 61 us for 250 rows of 4,000 and 122 for 1,000, and are for the rest.
   if (nc <= 64 * 4) topk_select_kernel<1, 4, true, kRead><<<four, kThreads, 0, stream>>>(a);
   else if (nc <= 64 * 10) topk_select_kernel<1, 10, true, kRead><<<four, kThreads, 0, stream>>>(a);
   else if (nc <= 64 * 16) topk_select_kernel<1, 16, true, kRead><<<four, kThreads, 0, stream>>>(a);
   else if (nc <= 64 * 32) topk_select_kernel<1, 32, true, kRead><<<four, kThreads, 0, stream>>>(a);
-  else if (nc <= 64 * 64) topk_select_kernel<1, 64, true, kRead><<<four, kThreads, 0, stream>>>(a);
+  else if (nc <= 64 * 64) topk_select_kernel<4, 16, true, kRead><<<rows, kThreads, 0, stream>>>(a);
   else topk_select_kernel<4, 64, true, kRead><<<rows, kThreads, 0, stream>>>(a);
   return hipGetLastError();
 }

@@ -91,8 +91,8 @@ def test_topk_lists_bit_exact(B, L, H, T, mc, pin, n, budget, keep_sink, keep_cu
 
 
 # The selection holds a row's keys in 1 register of one, two or four waves (few pairs,
-# scored in place), in 4, 10, 16, 32 or 64 registers per lane, then in four waves:
-# candidate counts at both sides of each limit.  With the same keys
+# scored in place), in 4, 10, 16 or 32 registers per lane, then in 16 or 64 of four
+# waves: candidate counts at both sides of each limit.  With the same keys
 # in every chunk each score occurs once per chunk, so the budget cuts through ties.
 @pytest.mark.parametrize("chunks,nt", [(2, 32), (5, 13), (2, 64), (3, 43), (4, 64), (1, 257), (10, 64), (1, 641), (16, 64), (25, 41), (32, 64), (3, 683),
                                        (64, 64), (17, 241)])
