@@ -501,7 +501,7 @@ def test_t64_tile_edges(L):
 
 
 # ... and a row's list is taken into LDS 1,024 entries at a time: 1,088 of them,
-# whole and in slices, with an odd number in the second part as well.
+# whole and in slices, and rows of fewer (an odd number in the second part as well).
 @pytest.mark.parametrize("p,split", [(1.0, None), (0.97, None), (1.0, (3, 5))])
 def test_t64_long_lists(p, split):
     P = require_gpu()
@@ -515,6 +515,30 @@ def test_t64_long_lists(p, split):
     o, lse = case.win.attention(q, 1 / math.sqrt(128), split=split)
     torch.cuda.synchronize()
     _sampled_check(case, rule, q, [(0, 0, r) for r in (0, 31, 32, 63, 200, 500, 1000, 1024)], o=o, lse=lse)
+
+
+def test_t64_long_list_odd_first_part():
+    """A stale entry among the first 1,024 leaves 1,023 tiles to the first part, after
+    which the two K buffers start from the first again (hand-made lists)."""
+    P = require_gpu()
+    log("attn t64 long list, stale entry in the first part")
+    case = Case(P, 1, 1025, 1, 64, 64, True, seed=1450, gen_device="cuda")
+    for _ in range(64):
+        case.append()
+    rule = case.rule(1.0)
+    case.gpu_lists(rule)
+    _, idx, _ = case.win.lists_views()
+    idx[..., 700] = 64 * 17                      # one past the window's last tile
+    q = case.query()
+    o, lse = case.attention(q)
+    bits = case.oracle_bits(rule).copy()
+    bits[..., 700] = False
+    samples = [(0, 0, r) for r in (0, 31, 32, 63, 500, 1024)]
+    O, LSE = oracle.sparse_causal_attention_rows(case.ring, case._host(q), bits, 64, 1 / math.sqrt(128), samples)
+    err = row_rel_err(f64(o)[0, [r for _, _, r in samples], 0], O)
+    lerr = float(np.abs(f64(lse)[0, 0, [r for _, _, r in samples]] - LSE).max())
+    log(f"  sampled rows={len(samples)} rel_err={err:.3e} lse_err={lerr:.3e}")
+    assert err <= REL_TOL and lerr <= lse_tol(64)
 
 
 def _bf16(x):

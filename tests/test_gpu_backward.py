@@ -129,9 +129,12 @@ def test_backward_half_tile_units(T, L, p):
     assert max(worst) <= GRAD_TOL, worst
 
 
-# The query-side kernel takes a row's list into LDS 1,024 entries at a time: lists
-# of 1,024 to 1,088 tiles (64 chunks), an odd number of units in the first part.
-@pytest.mark.parametrize("T,L,p", [(64, 1025, 1.0), (128, 2049, 1.0), (128, 1985, 1.0), (64, 1088, 0.95)])
+# The query-side kernel takes a row's list into LDS 1,024 entries at a time, and its two
+# buffers in turn: lists of 1,024 to 1,280 tiles (64 chunks) whose first part is 1,024 units
+# (64-token tiles), 1,988 and 2,048 units (even; the last has no second part), and 1,995 and
+# 1,997 (odd: the second part starts in the first buffer again).
+@pytest.mark.parametrize("T,L,p", [(64, 1025, 1.0), (128, 2049, 1.0), (128, 1985, 1.0), (64, 1088, 0.95),
+                                   (128, 2305, 1.0), (128, 2433, 1.0)])
 def test_backward_long_lists(T, L, p):
     P = require_gpu()
     log(f"bwd long lists T={T} L={L} p={p}")
