@@ -472,8 +472,20 @@ int uf_sparse_causal_attn_fwd_split(const uf_kv* kv, const void* d_q, const void
 int uf_attn_tail_plan(const uf_kv* kv, int32_t n_cu, int32_t* split_from, int32_t* n_split) {
   if (kv == nullptr || split_from == nullptr || n_split == nullptr) return fail(UF_ERR_ARG, "null argument");
   if (n_cu < 1) return fail(UF_ERR_ARG, "n_cu must be >= 1");
-  // rounds of one workgroup per CU (128-token tiles; three 64-token ones fit one
-  // CU, where the plan keeps the same count)
+  // Rounds of one workgroup per CU with either tile size.  Three 64-token workgroups
+  // fit one CU, but beside each other they share its copies and matrix cores, so
+  // rows past the last full round still cost time that slices save: 64-token tiles,
+  // whole / plan (split_from, n_split), us: 288 rows of 120 key tiles 107.6 / 101.1 (256, 8),
+  // 320 of 320 268 / 254 (256, 4), 384 of 288 261 / 251 (256, 2), 576 of 96 142 / 128 and of
+  // 384 538 / 472 (512, 4), 600 of 600 841 / 754 (512, 8), 832 of 320 649 / 543 (768, 4), 876
+  // of 292 601 / 520 (768, 7), 1,600 of 400 1,383 / 1,278 (1536, 4).  Where it declines, splitting
+  // loses too (256 rows of 64: 52.3 whole, 51.1 at best; 720 of 240: 364 against 367; 768 of
+  // 192: 305 against 314).  With fewer rows than CUs more slices than the plan's would
+  // pay (100 rows of 300: 211 whole, 118 in its two, 87 in six).
+  // 128-token tiles: 304 rows of 228 670 / 520 (256, 5), 528 of 264 1,246 / 1,026 (512, 8), 608
+  // of 608 2,940 / 2,682 (512, 8), 300 of 900 2,640 / 1,921 (256, 5), 52 of 156 178 / 78 (0, 4);
+  // declined: 444 of 148 496 against 507 at best, 720 of 240 1,245 against 1,280, 444 of 444
+  // 1,452 against 1,426 (under the 16 key tiles asked for), 456 of 608 2,028 against 2,077.
   const int64_t R = kv->layout().rows, C = int64_t(n_cu);
   *split_from = int32_t(R);
   *n_split = 1;
@@ -482,7 +494,8 @@ int uf_attn_tail_plan(const uf_kv* kv, int32_t n_cu, int32_t* split_from, int32_
   // rounds of 1/S row-time plus a slice's fixed cost, and the merge launch
   // follows (F = C * floor(R / C)).  The fixed costs, in key tiles of work
   // (a row of the window is taken as dense, nk tiles), are measured ones: a
-  // slice's prologue and epilogue about 9 tiles, the merge about 12.
+  // slice's prologue and epilogue about 9 tiles, the merge about 12 (it was three
+  // times as long then; the figures above are with the present one).
   constexpr double kSliceTiles = 9.0, kMergeTiles = 12.0;
   const int64_t q = R / C, r = R % C;
   if (r == 0) return ok();
