@@ -41,6 +41,7 @@ TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "attn_fwd_tri_1k_traffic.md")
 ATTN_SOURCES = ("paper_2606_09150_amd/csrc/kernels/attn_fwd_tri.hip",
                 "paper_2606_09150_amd/csrc/kernels/attn_common.h",
                 "paper_2606_09150_amd/csrc/kernels/kv_append.hip",
+                "paper_2606_09150_amd/csrc/xcd_order.h",
                 "paper_2606_09150_amd/csrc/launch.h")
 
 
