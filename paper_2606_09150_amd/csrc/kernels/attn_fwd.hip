@@ -23,7 +23,7 @@
 // waits: 12 heads, 4,665 tokens, four chunks, half of two of them kept, take
 // 477 us (840 TFLOP/s); one workgroup per CU whose two groups of two waves walked
 // alternate tiles in single buffers, one wave per SIMD, took 855 us (469).  The
-// smallest window (6 rows of 6 tiles) takes 9.9 us, 12.1 before.
+// smallest window (6 rows of 6 tiles) takes 10.4 us, 12.1 before.
 //
 // Memory: pages are copied HBM -> LDS by direct global_load_lds (16 bytes per
 // lane).  K lies in LDS as two blocks of 64 dimensions, V^T as one of 64 keys,
