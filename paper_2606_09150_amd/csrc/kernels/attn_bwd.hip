@@ -280,7 +280,8 @@ __global__ __launch_bounds__(4 * T, 2) void bwd_dkdv_kernel(BwdArgs a) {
   // position 0) are kept by every query tile and run longest
   const int rows = a.B * a.H * a.NT;
   const int order = int(blockIdx.x) / rows;
-  const int kj = xcd_item(int(blockIdx.x) - order * rows, rows, a.NT, T == 128 ? 256 : 512);
+  const int kj = xcd_deal(int(blockIdx.x) - order * rows, rows, rows, rows, rows * a.n_live, a.NT, T == 128 ? 256 : 512,
+                          a.counts);
   const int t = kj % a.NT;
   const int bh = kj / a.NT;
   const int pos = order == 0 ? a.n_live - 1 : order - 1;
@@ -646,7 +647,8 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_kernel(BwdArgs a) {
   __shared__ uint4 sbuf[2][kUnit / 16];        // K 16 KB, V^T 16 KB
   __shared__ uint32_t sunit[2 * kDqList + 1];  // (key tile << 1) | half; the count last
 
-  const int row = xcd_item(int(blockIdx.x), a.B * a.H * a.NT, a.NT, 512);   // (b*H + h)*NT + i
+  const int rows = a.B * a.H * a.NT;
+  const int row = xcd_deal(int(blockIdx.x), rows, rows, rows, rows, a.NT, 512, a.counts);   // (b*H + h)*NT + i
   const int i = row % a.NT;
   const int bh = row / a.NT;
   const int h = bh % a.H, b = bh / a.H;

@@ -62,6 +62,21 @@ __device__ __forceinline__ const uint8_t* uniform_ptr(const uint8_t* q) {
   return reinterpret_cast<const uint8_t*>(lo | (hi << 32));
 }
 
+// Item of workgroup i in a launch (or its part) whose items 0 .. whole-1 are whole rows
+// and the n - whole others slices of rows whole .. rows-1; the launch has `items`.
+// Contiguous ranges per XCD where heads are short enough for that to pay and no
+// XCD gets much more to do by it (xcd_order.h).  With no more items than CUs every
+// one has its own CU, whatever the order.
+__device__ __forceinline__ int xcd_deal(int i, int n, int whole, int rows, int items, int NT, int resident,
+                                        const int32_t* counts) {
+  if (NT * 4 > resident) return i;
+  if (items > 256) {
+    const bool slice = i >= whole;
+    if (!xcd_even((const const_i32*)counts + (slice ? whole : 0), slice ? rows - whole : whole)) return i;
+  }
+  return xcd_split_item(i, n, whole, NT, resident);
+}
+
 // s_waitcnt immediates (gfx9 encoding): vmcnt in [3:0] and [15:14], expcnt
 // in [6:4], lgkmcnt in [11:8].
 constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }

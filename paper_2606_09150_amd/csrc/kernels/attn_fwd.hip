@@ -80,8 +80,7 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_kernel(AttnArgs a) {
   // load at the head of the kernel, 0.5 us of a 42 us launch)
   const int rows = a.B * a.H * a.NT;
   const int grid = SPLIT ? a.split_from + (rows - a.split_from) * a.split : rows;
-  int row = SPLIT ? xcd_split_item(int(blockIdx.x), grid, a.split_from, a.NT, 3 * 256)
-                  : xcd_item(int(blockIdx.x), rows, a.NT, 3 * 256);
+  int row = xcd_deal(int(blockIdx.x), grid, SPLIT ? a.split_from : rows, rows, grid, a.NT, 3 * 256, a.counts);
   int part = 0;
   bool partial = false;
   if (SPLIT && row >= a.split_from) {

@@ -264,8 +264,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_tri_kernel(AttnArgs a) {
   // load at the head of the kernel, 0.5 us of a 42 us launch)
   const int rows = a.B * a.H * a.NT;
   const int grid = SPLIT ? a.split_from + (rows - a.split_from) * a.split : rows;
-  int row = SPLIT ? xcd_split_item(int(blockIdx.x), grid, a.split_from, a.NT, 256)
-                  : xcd_item(int(blockIdx.x), rows, a.NT, 256);
+  int row = xcd_deal(int(blockIdx.x), grid, SPLIT ? a.split_from : rows, rows, grid, a.NT, 256, a.counts);
   int part = 0;
   bool partial = false;               // this workgroup writes a split-KV partial
   if (SPLIT && row >= a.split_from) {

@@ -324,6 +324,32 @@ def test_empty_rows_and_stale_entries(T):
     assert np.abs(lf[fin] - LSE[fin]).max() <= lse_tol(T)
 
 
+# Heads with lists of their own lengths: more rows than CUs, long heads first, so that
+# the rows keep the grid's order (they go to the XCDs in ranges where lists are even).
+@pytest.mark.parametrize("T,split", [(64, None), (128, None), (64, (200, 2)), (128, (288, 3))])
+def test_heads_of_uneven_lists(T, split):
+    P = require_gpu()
+    log(f"attn uneven heads T={T} split={split}")
+    H, nt = 50, 6
+    case = Case(P, 1, T * nt - 5, H, T, 2, True, seed=1600 + T, gen_device="cuda")
+    for _ in range(2):
+        case.append()
+    case.gpu_lists(case.rule(1.0))
+    counts, _, _ = case.win.lists_views()
+    counts[:, 12:] = 1
+    bits = np.zeros((1, H, nt, 2 * nt), dtype=bool)
+    bits[:, :12] = True
+    bits[..., 0] = True
+    q = case.query()
+    o, lse = case.win.attention(q, split=split)
+    heads = [0, 11, 12, 31, 49]
+    O, LSE = oracle.sparse_causal_attention(head_ring(case.ring, heads), f64(q)[:, :, heads], bits[:, heads], T,
+                                            1 / math.sqrt(128))
+    err, lerr = row_rel_err(f64(o)[:, :, heads], O), float(np.abs(f64(lse)[:, heads] - LSE).max())
+    log(f"  rel_err={err:.3e} lse_err={lerr:.3e}")
+    assert err <= REL_TOL and lerr <= lse_tol(T)
+
+
 def test_lse_optional_and_outputs_untouched_beyond_shape():
     P = require_gpu()
     case = Case(P, 1, 200, 2, 128, 2, False, seed=9)

@@ -151,6 +151,36 @@ def test_backward_long_lists(T, L, p):
     assert err <= GRAD_TOL
 
 
+# Heads with lists of their own lengths: more rows (and key tiles) than CUs, long heads
+# first, so that both kernels keep the grid's order.
+@pytest.mark.parametrize("T", [64, 128])
+def test_backward_heads_of_uneven_lists(T):
+    P = require_gpu()
+    log(f"bwd uneven heads T={T}")
+    H, nt = 50, 6
+    case = Case(P, 1, T * nt - 5, H, T, 2, True, seed=2480 + T, gen_device="cuda")
+    for _ in range(2):
+        case.append()
+    case.gpu_lists(case.rule(1.0))
+    counts, _, mask = case.win.lists_views()
+    counts[:, 12:] = 1
+    mask[:, 12:] = 1
+    bits = np.zeros((1, H, nt, 2 * nt), dtype=bool)
+    bits[:, :12] = True
+    bits[..., 0] = True
+    q, do = case.query(), case._draw(case.n_appended - 1, "do")
+    o, lse = case.win.attention(q)
+    grads = case.win.attention_bwd(q, o, lse, do)
+    heads = [0, 11, 12, 31, 49]
+    ring = head_ring(case.ring, heads)
+    args = (ring, f64(q)[:, :, heads], f64(do)[:, :, heads], bits[:, heads], T, 1 / math.sqrt(128))
+    refs = oracle.sparse_causal_attention_bwd(*args)
+    scales = oracle.sparse_causal_attention_bwd_scales(*args)
+    worst = [float(row_errors_scaled(g.cpu().numpy()[..., heads, :], r, s).max()) for g, r, s in zip(grads, refs, scales)]
+    log("  per-row " + " ".join(f"{x:.3e}" for x in worst))
+    assert max(worst) <= GRAD_TOL, worst
+
+
 def test_backward_tiny_workload():
     """The tiny window (64-token tiles, 2 heads, 384 keys, every tile kept) in full."""
     P = require_gpu()

@@ -16,6 +16,12 @@ PROGRAM = r"""
 #include "list_rule.h"
 #include "xcd_order.h"
 int main(int c, char** v) {
+  if (c == 2) {                             // list lengths on standard input
+    static int counts[1 << 16];
+    for (int i = 0; i < atoi(v[1]); ++i)
+      if (scanf("%d", counts + i) != 1) return 1;
+    return printf("%d\n", int(uf::xcd_even(counts, atoi(v[1])))) < 0;
+  }
   if (c == 4) return printf("%d\n", int(uf::topk_row_alone(atoi(v[2]), atoi(v[3])))) < 0;
   if (c == 3) return printf("%d\n", int(uf::lists_wave_per_row(atoi(v[1]), atoi(v[2])))) < 0;
   const int n = atoi(v[1]), whole = atoi(v[2]), nt = atoi(v[3]), resident = atoi(v[4]);
@@ -30,7 +36,8 @@ def rules(tmp_path_factory):
     (d / "order.cpp").write_text(PROGRAM)
     exe = str(d / "order")
     subprocess.run(["g++", "-std=c++17", f"-I{CSRC}", str(d / "order.cpp"), "-o", exe], check=True)
-    return lambda *args: [int(x) for x in subprocess.check_output([exe, *map(str, args)]).split()]
+    return lambda *args, stdin="": [int(x) for x in subprocess.check_output([exe, *map(str, args)],
+                                                                             input=stdin.encode()).split()]
 
 
 # (rows, rows kept whole, slices of each other row, rows of a head, resident workgroups)
@@ -53,6 +60,22 @@ def test_whole_rows_and_slices_are_dealt_alike_to_every_xcd(rules, rows, whole, 
         for it in on_xcd:
             for kind in ([i for i in it if i < whole], [i for i in it if i >= whole]):
                 assert not kind or kind == list(range(kind[0], kind[0] + len(kind)))
+
+
+def _lengths(heads, nt, long, every, few, full=400):
+    """List lengths of `heads` heads of nt rows; `long` of them (each `every`-th head) are full."""
+    return [full if h % every == 0 and h // every < long else few for h in range(heads) for _ in range(nt)]
+
+
+# A contiguous range of rows per XCD is taken only where it gives no XCD much more to do.
+@pytest.mark.parametrize("counts,even", [
+    (_lengths(12, 37, 12, 1, 0), 1), (_lengths(1, 257, 1, 1, 0), 1), ([0] * 300, 1), ([400, 399, 401] * 100, 1),
+    ([90 + (7 * i * i) % 11 for i in range(888)], 1), (_lengths(80, 16, 40, 2, 40), 1),
+    (_lengths(16, 19, 2, 1, 40), 0), (_lengths(16, 33, 4, 1, 40), 0), (_lengths(16, 33, 4, 4, 40), 0),
+    (_lengths(16, 64, 4, 1, 40), 0), (_lengths(12, 73, 3, 1, 120), 0), ([0] * 280 + [400] * 20, 0),
+    ([400] * 300 + [200] * 300, 0)])
+def test_rows_go_to_xcds_in_ranges_only_with_even_lists(rules, counts, even):
+    assert rules(len(counts), stdin=" ".join(map(str, counts))) == [even]
 
 
 # (rows, key tiles of a row, a wave per row): where one side was at least 4 % faster
